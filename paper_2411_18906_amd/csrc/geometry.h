@@ -71,6 +71,11 @@ struct ChainState {
     int32_t done;
     int32_t status;
     double S, F;   // objective of the final counts (Eq. 3), written after the run
+    // Window of a chain that has gone quiet (mc_kernels.hip): its length in
+    // steps (0: none), and the first of its steps that holds an improving
+    // candidate (scan_steps: none does), found by the scan kernel.
+    int32_t scan_steps;
+    int32_t scan_found;
 };
 
 enum SpeciesStore : int32_t {
@@ -104,6 +109,9 @@ struct ChainDesc {
     double w[kMaxShells];
     int8_t *species;       // [N] unpadded configuration, in/out
     int8_t *pad_global;    // [Npad] padded copy when store == kStoreGlobal
+    uint8_t *image;        // the LDS store of a chain that has gone quiet (16-byte aligned), or null
+    uint8_t *scan_nulls;   // [scan_cap] null draws per slot group of a scanned window, or null
+    int32_t scan_cap;      // slot groups a scanned window may hold
     const double *R;       // [S][M][M]
     const double *target;  // [S][M][M]
     int32_t *counts;       // [S][M][M] maintained pair counts, in/out

@@ -30,7 +30,7 @@ __host__ __device__ inline int mc_lds_bytes(int S, int M, int B, int W = 0, int 
 }
 
 // bytes of the species store for a padded chain
-inline int64_t species_store_bytes(int store, int64_t Npad) {
+__host__ __device__ inline int64_t species_store_bytes(int store, int64_t Npad) {
     if (store == kStoreLds8) return (Npad + 15) & ~int64_t(15);
     if (store == kStoreLds4) return (((Npad + 7) / 8) * 4 + 15) & ~int64_t(15);
     return 0;
@@ -46,8 +46,18 @@ int mc_block_threads(int B, int W, int K);
 constexpr int kMaxLookahead = 8;
 
 // One launch of n_chains chains (one block each) for up to max_steps steps.
+// quiet > 0 (chains with image or pad_global, scan_nulls and scan_cap set): a
+// chain also ends its launch, with a window to scan, once `quiet` steps in a row
+// committed nothing.
 hipError_t launch_mc(const ChainDesc *descs_dev, int n_chains, int store, int M, int S, int B, int W, int bal,
-                     int K, int CH, int lds_bytes, int max_steps, hipStream_t stream);
+                     int K, int CH, int lds_bytes, int max_steps, hipStream_t stream, int quiet = 0);
+
+// The windows of quiet chains (chains without one are skipped), each by
+// blocks_per_chain blocks; store_bytes: the largest LDS store of the chains.
+constexpr int kScanThreads = 512;
+inline int scan_lds_bytes(int S, int M) { return S * M * M * 32 + kMaxOffsets * 16; }
+hipError_t launch_scan(const ChainDesc *descs_dev, int n_chains, int store, int M, int store_bytes, int S,
+                       int blocks_per_chain, hipStream_t stream);
 // Ratio tables of chains from their initial counts (descriptor order; bad [n]
 // the invalid-id flags in the same order); invalid chains get status EINVAL.
 hipError_t launch_chain_ratio(const ChainDesc *descs_dev, int n_chains, const int32_t *bad, hipStream_t stream);

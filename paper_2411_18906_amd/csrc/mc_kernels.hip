@@ -200,6 +200,61 @@ __device__ void write_site(const Lds &L, const ChainDesc &d, int cx, int cy, int
             for (int px = x0; px < d.PX; px += d.Lx) store_species<kStore>(L, d, padded_id(d, px, py, pz, b), v);
 }
 
+// dQ_k = sum over rows i of (sum over j of sq(N + dN) - sq(N)) of swapping
+// species a at p with b at q, whose shell-k neighbour histograms (partner
+// removed) are cp and cq; ent are the shell's entries.
+template <int M, typename Hist>
+__device__ __forceinline__ double shell_dQ(const Ent *ent, Hist cp, Hist cq, int a, int b, int sym) {
+    double dQ = 0.0;
+    // D = c_q - c_p and u = +1 at species a, -1 at b: dN[i][j] = u_i D_j + u_j D_i
+    int D[M], u[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        D[j] = fld(cq, j) - fld(cp, j);
+        u[j] = (j == a ? 1 : 0) - (j == b ? 1 : 0);
+    }
+    if (sym) {
+        // Symmetric N, dN, R and target: only rows lo = min(a, b) and
+        // hi = max(a, b) need evaluating; row i of the others holds
+        // nonzero terms only at columns lo < hi, equal to entries
+        // (lo, i) and (hi, i).  Terms with dN = 0 are exactly +0.0.
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        const int ulo = lo == a ? 1 : -1;
+        const int Dlo = fld(cq, lo) - fld(cp, lo), Dhi = fld(cq, hi) - fld(cp, hi);
+        const Ent *elo = ent + lo * M, *ehi = ent + hi * M;
+        double ro[M];   // row j's sum when j is neither lo nor hi
+        double rlo = 0.0, rhi = 0.0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const Ent e1 = elo[j];
+            const int n1 = __mul24(ulo, D[j]) + __mul24(u[j], Dlo);
+            const double dl = sq_dev(e1.cnt + n1, e1.R, e1.t) - e1.sq;
+            const Ent e2 = ehi[j];
+            const int n2 = __mul24(-ulo, D[j]) + __mul24(u[j], Dhi);
+            const double dh = sq_dev(e2.cnt + n2, e2.R, e2.t) - e2.sq;
+            rlo = rlo + dl;
+            rhi = rhi + dh;
+            ro[j] = dl + dh;
+        }
+#pragma unroll
+        for (int i = 0; i < M; ++i) dQ = dQ + (i == lo ? rlo : (i == hi ? rhi : ro[i]));
+    } else {
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            double rs = 0.0;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const Ent en = ent[i * M + j];
+                const int dn = __mul24(u[i], D[j]) + __mul24(u[j], D[i]);
+                const double sn = sq_dev(en.cnt + dn, en.R, en.t);
+                rs = rs + (sn - en.sq);
+            }
+            dQ = dQ + rs;
+        }
+    }
+    return dQ;
+}
+
 // change of entry (i, j) of shell k's counts when candidate s (record index) commits
 template <int M, typename Hist>
 __device__ __forceinline__ int entry_dn(const Lds &L, int Bt, int r, int k, int i, int j) {
@@ -225,9 +280,13 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+constexpr int kShNulls = 24;    // sh_int slot: null draws of a scanned window
+constexpr int kMinScan = 48;    // steps left below which a quiet chain finishes by itself
+
 template <int kStore, int M>
 __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ descs,
-                                                  int32_t max_steps, int32_t W, int32_t bal, int32_t K, int32_t CH) {
+                                                  int32_t max_steps, int32_t W, int32_t bal, int32_t K, int32_t CH,
+                                                  int32_t quiet) {
     using Hist = typename HistT<(M > 6)>::type;
     const ChainDesc &d = descs[blockIdx.x];
     ChainState *st = d.state;
@@ -293,7 +352,13 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
     for (int t = threadIdx.x; t < kMaxOffsets; t += nthreads)
         L.dlin4[t] = make_int4(d.dlin[0][t], d.dlin[1][t], d.dlin[2][t], d.dlin[3][t]);
     for (int t = threadIdx.x; t < kMaxOffsets; t += nthreads) L.offmod[t] = d.off_mod[t];
-    if constexpr (kStore != kStoreGlobal) {
+    const int scan_steps = st->scan_steps;   // > 0: back from a scanned window
+    if (kStore != kStoreGlobal && scan_steps > 0) {
+        const int nv = (int)(species_store_bytes(kStore, d.Npad) / 16);
+        const uint4 *src = reinterpret_cast<const uint4 *>(d.image);
+        uint4 *dst = reinterpret_cast<uint4 *>(L.store);
+        for (int i = threadIdx.x; i < nv; i += nthreads) dst[i] = src[i];
+    } else if constexpr (kStore != kStoreGlobal) {
         // fill the halo-padded configuration from the unpadded one
         const double inv_PX = 1.0 / (double)d.PX, inv_PY = 1.0 / (double)d.PY;
         const int h = d.halo;
@@ -321,6 +386,7 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
             }
         }
     }
+    if (threadIdx.x == 0) L.sh_int[kShNulls] = 0;
     __syncthreads();
 
     // chain counters: identical copies in every thread
@@ -350,7 +416,47 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
     // evaluates one step.
     int kpref = K;
     int64_t steps_run = 0;
+    // A quiet chain hands its next steps to the scan kernel: with quiet > 0 it
+    // leaves once `quiet` steps in a row committed nothing and at least
+    // kMinScan are left, and comes back at the first step of the scanned window
+    // that holds an improving candidate (or at its end).  The steps before it
+    // commit nothing: only their counters move on.
+    int quiet_run = 0;
+    if (scan_steps > 0) {
+        const int adv = st->scan_found;
+        int32_t sum = 0;
+        const int ng = adv * Gs;
+        for (int i = threadIdx.x; i < ng; i += nthreads) sum += d.scan_nulls[i];
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) sum += __shfl_xor(sum, m);
+        if (lane == 0) atomicAdd(&L.sh_int[kShNulls], sum);
+        __syncthreads();
+        nulls += L.sh_int[kShNulls];
+        trials = min(trials + (int64_t)adv * B, d.n_trials);
+        step += adv;
+        depth += adv;
+        if (d.depth_limit > 0 && depth >= d.depth_limit) {
+            stop_reason = PYHEA_STOP_DEPTH;
+            done = true;
+        } else if (trials >= d.n_trials) {
+            stop_reason = PYHEA_STOP_TRIALS;
+            done = true;
+        }
+        if (adv < scan_steps)
+            kpref = 1;          // this step commits
+        else
+            quiet_run = quiet;  // the window's end: scan on
+    }
+    int scan_next = 0;
     while (!done && steps_run < max_steps) {
+        if (quiet > 0 && quiet_run >= quiet) {
+            int64_t left = (d.n_trials - trials + B - 1) / B;
+            if (d.depth_limit > 0) left = min(left, (int64_t)(d.depth_limit - depth));
+            if (left >= kMinScan) {
+                scan_next = (int)min(left, (int64_t)(d.scan_cap / Gs));
+                break;
+            }
+        }
         const int ke = (int)min((int64_t)kpref, (int64_t)max_steps - steps_run);
 
         // ---- phase 1: draw and evaluate (step offset kw, slot) --------------------------
@@ -476,54 +582,7 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
                 }
                 cp -= (Hist)m << (5 * b);
                 cq -= (Hist)m << (5 * a);
-                // D = c_q - c_p and u = +1 at species a, -1 at b: dN[i][j] = u_i D_j + u_j D_i
-                int D[M], u[M];
-#pragma unroll
-                for (int j = 0; j < M; ++j) {
-                    D[j] = fld(cq, j) - fld(cp, j);
-                    u[j] = (j == a ? 1 : 0) - (j == b ? 1 : 0);
-                }
-                // dQ_k = sum over rows i of (sum over j of sq(N + dN) - sq(N))
-                if (d.sym) {
-                    // Symmetric N, dN, R and target: only rows lo = min(a, b) and
-                    // hi = max(a, b) need evaluating; row i of the others holds
-                    // nonzero terms only at columns lo < hi, equal to entries
-                    // (lo, i) and (hi, i).  Terms with dN = 0 are exactly +0.0.
-                    const int lo = a < b ? a : b, hi = a < b ? b : a;
-                    const int ulo = lo == a ? 1 : -1;
-                    const int Dlo = fld(cq, lo) - fld(cp, lo), Dhi = fld(cq, hi) - fld(cp, hi);
-                    const Ent *elo = L.ent + (k * M + lo) * M, *ehi = L.ent + (k * M + hi) * M;
-                    double ro[M];   // row j's sum when j is neither lo nor hi
-                    double rlo = 0.0, rhi = 0.0;
-#pragma unroll
-                    for (int j = 0; j < M; ++j) {
-                        const Ent e1 = elo[j];
-                        const int n1 = __mul24(ulo, D[j]) + __mul24(u[j], Dlo);
-                        const double dl = sq_dev(e1.cnt + n1, e1.R, e1.t) - e1.sq;
-                        const Ent e2 = ehi[j];
-                        const int n2 = __mul24(-ulo, D[j]) + __mul24(u[j], Dhi);
-                        const double dh = sq_dev(e2.cnt + n2, e2.R, e2.t) - e2.sq;
-                        rlo = rlo + dl;
-                        rhi = rhi + dh;
-                        ro[j] = dl + dh;
-                    }
-#pragma unroll
-                    for (int i = 0; i < M; ++i) dQ = dQ + (i == lo ? rlo : (i == hi ? rhi : ro[i]));
-                } else {
-                    const Ent *row = L.ent + k * M * M;
-#pragma unroll
-                    for (int i = 0; i < M; ++i) {
-                        double rs = 0.0;
-#pragma unroll
-                        for (int j = 0; j < M; ++j) {
-                            const Ent en = row[i * M + j];
-                            const int dn = __mul24(u[i], D[j]) + __mul24(u[j], D[i]);
-                            const double sn = sq_dev(en.cnt + dn, en.R, en.t);
-                            rs = rs + (sn - en.sq);
-                        }
-                        dQ = dQ + rs;
-                    }
-                }
+                dQ = shell_dQ<M>(L.ent + k * M * M, cp, cq, a, b, d.sym);
             }
             if (k >= 0 && slot < B && kw < ke) {
                 ((Hist *)L.rec_cp)[k * Bt + rix] = cp;
@@ -620,12 +679,14 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
                 done = true;
             }
         }
+        quiet_run += pass_steps;
         if (done || kstar >= ke) {
             steps_run += pass_steps;
             kpref = K;
             __syncthreads();
             continue;
         }
+        quiet_run = 0;
         const int rb = kstar * B;   // records of the committing step
         const int tasks = (int)min((int64_t)B, d.n_trials - trials);
 
@@ -893,7 +954,12 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
 
     // ---- write back -------------------------------------------------------------------
     for (int e = threadIdx.x; e < E; e += nthreads) d.counts[e] = L.ent[e].cnt;
-    if constexpr (kStore != kStoreGlobal) {
+    if (kStore != kStoreGlobal && scan_next > 0) {
+        const int nv = (int)(species_store_bytes(kStore, d.Npad) / 16);
+        const uint4 *src = reinterpret_cast<const uint4 *>(L.store);
+        uint4 *dst = reinterpret_cast<uint4 *>(d.image);
+        for (int i = threadIdx.x; i < nv; i += nthreads) dst[i] = src[i];
+    } else if constexpr (kStore != kStoreGlobal) {
         for (uint32_t p = threadIdx.x; p < d.N; p += nthreads) {
             const SiteCoord c = site_coord(p, d.lgA, d.Lx, d.Ly, d.inv_Lx, d.inv_Ly);
             d.species[p] = (int8_t)load_species<kStore>(L, d, padded_id(d, c.cx + h, c.cy + h, c.cz + h, c.b));
@@ -905,6 +971,8 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
         st->steps = step;
         st->null_trials = nulls;
         st->depth = depth;
+        st->scan_steps = scan_next;
+        st->scan_found = scan_next;
         if (done) {
             st->stop_reason = stop_reason;
             st->done = 1;
@@ -912,13 +980,152 @@ __global__ void __launch_bounds__(1024) mc_kernel(const ChainDesc *__restrict__ 
     }
 }
 
-// padded HBM copy <-> unpadded configuration (HBM-resident chains)
+// The steps of a quiet chain's window, evaluated by the whole chip.  While
+// nothing commits, the candidates of all later steps are evaluated against the
+// same state (they are drawn from counters), so the steps of the window are
+// independent: a wavefront takes one slot group (64 candidates of a step), a
+// lane one candidate with all its shells, and no barrier is needed.  A group
+// with an improving candidate lowers scan_found to its step; groups of later
+// steps are skipped from then on, and every group of an earlier step is always
+// evaluated, so that scan_found ends as the first such step and the null draws
+// of all steps before it are complete.  dS is formed by the expressions of
+// mc_kernel's phases 1 and 2 in the same order.
+//
+// Bound: VALU and LDS issue of the evaluation, spread over every CU instead of
+// one.  FCC 20^3, 5 species, 3 shells, 10^6 trials (61 committing steps of
+// 15,625, the last 30 of them far apart): 22.7 ms with every step on one CU, 1.9
+// ms with windows (the first, commit-heavy 120 steps take 0.78 ms of it, a
+// round of scan and chain 30 + 38 us); FCC 40^3, 10^7 trials: 244 -> 25 ms.
+template <int kStore, int M>
+__global__ void __launch_bounds__(kScanThreads) scan_kernel(const ChainDesc *__restrict__ descs) {
+    using Hist = typename HistT<(M > 6)>::type;
+    const ChainDesc &d = descs[blockIdx.y];
+    ChainState *st = d.state;
+    const int n_steps = st->scan_steps;
+    if (st->done || n_steps == 0) return;
+    const int S = d.S, E = S * M * M, B = d.B;
+    const int Gs = (B + kWave - 1) / kWave;
+    const int n_items = n_steps * Gs;
+    constexpr int kWaves = kScanThreads / kWave;
+    if ((int)blockIdx.x * kWaves >= n_items) return;
+    const int lane = threadIdx.x % kWave;
+    extern __shared__ __align__(16) uint8_t smem[];
+    Lds L;
+    {
+        uint8_t *p = smem;
+        L.ent = (Ent *)carve(p, E * sizeof(Ent));
+        L.dlin4 = (int4 *)carve(p, kMaxOffsets * 16);
+        L.store = p;
+    }
+    for (int e = threadIdx.x; e < E; e += kScanThreads) {
+        Ent en;
+        en.cnt = d.counts[e];
+        en.R = d.R[e];
+        en.t = d.target[e];
+        en.sq = sq_dev(en.cnt, en.R, en.t);
+        en.pad = 0;
+        L.ent[e] = en;
+    }
+    for (int t = threadIdx.x; t < kMaxOffsets; t += kScanThreads)
+        L.dlin4[t] = make_int4(d.dlin[0][t], d.dlin[1][t], d.dlin[2][t], d.dlin[3][t]);
+    if constexpr (kStore != kStoreGlobal) {
+        const int nv = (int)(species_store_bytes(kStore, d.Npad) / 16);
+        const uint4 *src = reinterpret_cast<const uint4 *>(d.image);
+        uint4 *dst = reinterpret_cast<uint4 *>(L.store);
+        for (int i = threadIdx.x; i < nv; i += kScanThreads) dst[i] = src[i];
+    }
+    __syncthreads();
+
+    const int64_t trials = st->trials;
+    const uint32_t step0 = (uint32_t)st->steps;
+    const uint32_t key0 = (uint32_t)d.seed, key1 = (uint32_t)(d.seed >> 32);
+    const int h = d.halo;
+    const double tau = d.tau;
+    const int stride = (int)gridDim.x * kWaves;
+    int found = n_steps;   // read one item late: a stale value only costs work
+#pragma unroll 1
+    for (int it = (int)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); it < n_items;
+         it += stride) {
+        const int rel = it / Gs;
+        if (rel > found) break;
+        const int seen = __hip_atomic_load(&st->scan_found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int slot = (it - rel * Gs) * kWave + lane;
+        const int64_t left = d.n_trials - trials - (int64_t)rel * B;
+        const bool active = slot < B && slot < left;
+        bool null_draw = false, imp = false;
+        if (active) {
+            uint32_t c[4] = {(uint32_t)slot, step0 + (uint32_t)rel, d.chain_id, 0u};
+            philox4x32_10(c, key0, key1);
+            const uint32_t p = __umulhi(c[0], d.N), q = __umulhi(c[1], d.N);
+            const SiteCoord sp = site_coord(p, d.lgA, d.Lx, d.Ly, d.inv_Lx, d.inv_Ly);
+            const SiteCoord sq = site_coord(q, d.lgA, d.Lx, d.Ly, d.inv_Lx, d.inv_Ly);
+            const int32_t pidp = padded_id(d, sp.cx + h, sp.cy + h, sp.cz + h, sp.b);
+            const int32_t pidq = padded_id(d, sq.cx + h, sq.cy + h, sq.cz + h, sq.b);
+            const int a = load_species<kStore>(L, d, pidp), b = load_species<kStore>(L, d, pidq);
+            null_draw = a == b;
+            if (!null_draw) {
+                int bx, by, bz;
+                basis_bits(d.A, sp.b, bx, by, bz);
+                const uint32_t ppos = pack_pos(2 * sp.cx + bx, 2 * sp.cy + by, 2 * sp.cz + bz);
+                basis_bits(d.A, sq.b, bx, by, bz);
+                const uint32_t qpos = pack_pos(2 * sq.cx + bx, 2 * sq.cy + by, 2 * sq.cz + bz);
+                const int32_t *dlp = reinterpret_cast<const int32_t *>(L.dlin4) + sp.b;
+                const int32_t *dlq = reinterpret_cast<const int32_t *>(L.dlin4) + sq.b;
+                const int r2 = d.small_cell ? -1 : min_image_r2(d, ppos, qpos);
+                const int32_t md = d.small_cell ? mod_delta(d, ppos, qpos) : 0;
+                double dS = 0.0;
+#pragma unroll 1
+                for (int k = 0; k < S; ++k) {
+                    const int t0 = d.zstart[k], t1 = d.zstart[k + 1];
+                    Hist cp = 0, cq = 0;
+                    constexpr int kU = 6;   // shells hold 6, 8, 12 or 24 offsets
+                    int t = t0;
+#pragma unroll 1
+                    for (; t + kU <= t1; t += kU) {
+                        int vp[kU], vq[kU];
+#pragma unroll
+                        for (int u = 0; u < kU; ++u) {
+                            vp[u] = load_species<kStore>(L, d, pidp + dlp[(t + u) * 4]);
+                            vq[u] = load_species<kStore>(L, d, pidq + dlq[(t + u) * 4]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < kU; ++u) {
+                            cp += one_at<Hist>(vp[u]);
+                            cq += one_at<Hist>(vq[u]);
+                        }
+                    }
+#pragma unroll 1
+                    for (; t < t1; ++t) {
+                        cp += one_at<Hist>(load_species<kStore>(L, d, pidp + dlp[t * 4]));
+                        cq += one_at<Hist>(load_species<kStore>(L, d, pidq + dlq[t * 4]));
+                    }
+                    int m = r2 == d.r2[k] ? 1 : 0;
+                    if (d.small_cell)
+                        for (int tt = t0; tt < t1; ++tt) m += d.off_mod[tt] == md ? 1 : 0;
+                    cp -= (Hist)m << (5 * b);
+                    cq -= (Hist)m << (5 * a);
+                    dS = dS + d.w[k] * shell_dQ<M>(L.ent + k * M * M, cp, cq, a, b, d.sym);
+                }
+                imp = dS < -tau;
+            }
+        }
+        const uint64_t any = ballot64(imp);
+        const int nnull = (int)__popcll(ballot64(null_draw));
+        if (lane == 0) {
+            d.scan_nulls[it] = (uint8_t)nnull;
+            if (any) atomicMin(&st->scan_found, rel);
+        }
+        found = any ? min(seen, rel) : seen;
+    }
+}
+
 // Chain states of many chains into one contiguous array (one read-back).
 __global__ void gather_states_kernel(const ChainDesc *__restrict__ descs, int n, ChainState *__restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] = *descs[i].state;
 }
 
+// padded HBM copy <-> unpadded configuration (HBM-resident chains)
 __global__ void pad_fill_kernel(const ChainDesc *__restrict__ descs) {
     const ChainDesc &d = descs[blockIdx.y];
     if (d.store != kStoreGlobal || d.state->status != 0) return;
@@ -959,7 +1166,7 @@ const void *mc_fn(int M) {
 }
 
 hipError_t launch_mc(const ChainDesc *descs_dev, int n_chains, int store, int M, int S, int B, int W, int bal,
-                     int K, int CH, int lds_bytes, int max_steps, hipStream_t stream) {
+                     int K, int CH, int lds_bytes, int max_steps, hipStream_t stream, int quiet) {
     if (mc_block_threads(B, W, K) > 1024 || K < 1 || K > kMaxLookahead || W < S || (!bal && W != S) || CH < 0 ||
         CH > 16)
         return hipErrorInvalidValue;
@@ -969,8 +1176,35 @@ hipError_t launch_mc(const ChainDesc *descs_dev, int n_chains, int store, int M,
                                            : mc_fn<kStoreGlobal>(M);
     hipError_t e = set_max_lds(fn, lds_bytes);
     if (e != hipSuccess) return e;
-    void *args[] = {(void *)&descs_dev, (void *)&max_steps, (void *)&W, (void *)&bal, (void *)&K, (void *)&CH};
+    void *args[] = {(void *)&descs_dev, (void *)&max_steps, (void *)&W, (void *)&bal, (void *)&K, (void *)&CH,
+                    (void *)&quiet};
     return hipLaunchKernel(fn, grid, block, args, (size_t)lds_bytes, stream);
+}
+
+template <int kStore>
+const void *scan_fn(int M) {
+    switch (M) {
+        case 2: return (const void *)scan_kernel<kStore, 2>;
+        case 3: return (const void *)scan_kernel<kStore, 3>;
+        case 4: return (const void *)scan_kernel<kStore, 4>;
+        case 5: return (const void *)scan_kernel<kStore, 5>;
+        case 6: return (const void *)scan_kernel<kStore, 6>;
+        case 7: return (const void *)scan_kernel<kStore, 7>;
+        default: return (const void *)scan_kernel<kStore, 8>;
+    }
+}
+
+hipError_t launch_scan(const ChainDesc *descs_dev, int n_chains, int store, int M, int store_bytes, int S,
+                       int blocks_per_chain, hipStream_t stream) {
+    if (n_chains < 1 || n_chains > 65535 || blocks_per_chain < 1) return hipErrorInvalidValue;
+    const void *fn = store == kStoreLds8 ? scan_fn<kStoreLds8>(M)
+                     : store == kStoreLds4 ? scan_fn<kStoreLds4>(M)
+                                           : scan_fn<kStoreGlobal>(M);
+    const size_t lds = (size_t)scan_lds_bytes(S, M) + (size_t)store_bytes;
+    hipError_t e = set_max_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    void *args[] = {(void *)&descs_dev};
+    return hipLaunchKernel(fn, dim3(blocks_per_chain, n_chains), dim3(kScanThreads), args, lds, stream);
 }
 
 hipError_t launch_gather_states(const ChainDesc *descs_dev, int n_chains, ChainState *out, hipStream_t stream) {

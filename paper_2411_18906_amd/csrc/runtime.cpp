@@ -651,6 +651,24 @@ hipError_t record_plan(ChainPlan *p, Work &work) {
     return e;
 }
 
+// Calls that scan (run_chains): chains at most, steps of the longest at least.
+// Below kWideSteps the launches cost more than the scan saves (FCC 4^3, 157
+// steps: 337 us per call without, 333 us with it); many chains keep the CUs busy
+// by themselves, and the windows of more chains than kWideChains would wait for
+// the slowest chain of each round.
+constexpr int kWideChains = 16;
+constexpr int kWideSteps = 128;
+// Steps without a commit after which a chain goes to the scan: a round (two
+// launches, the LDS fills, one evaluation) costs about as much as these steps on
+// one CU.
+constexpr int kQuietSteps = 16;
+// Rounds launched without a look at the chains' states, for chains of fewer and
+// of kManySteps steps or more.
+constexpr int kManySteps = 1024;
+constexpr int kRoundsShort = 4;
+constexpr int kRoundsLong = 16;
+constexpr int kScanCap = 1 << 16;   // slot groups of one window
+
 }  // namespace
 
 pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
@@ -755,7 +773,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     // launch whose longest chain is longest (per-trial cost taken as offsets
     // gathered plus count entries evaluated) goes first, so it starts first
     struct Launch {
-        int first, count, store, M, S, B, W, bal, K, CH, lds;
+        int first, count, store, M, S, B, W, bal, K, CH, lds, store_bytes;
     };
     std::vector<Launch> launches;
     std::vector<int> pos(n);   // descriptor position of each chain
@@ -774,10 +792,11 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
             });
             Launch L{at, (int)idx.size(), std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first),
                      std::get<3>(kv.first), std::get<4>(kv.first), std::get<5>(kv.first), std::get<6>(kv.first),
-                     std::get<7>(kv.first), 0};
+                     std::get<7>(kv.first), 0, 0};
             int64_t w = 0;
             for (int c : idx) {
                 L.lds = std::max(L.lds, shape[c].lds);
+                L.store_bytes = std::max(L.store_bytes, (int)species_store_bytes(shape[c].store, jobs[c].g.Npad));
                 pos[c] = at++;
                 const Geometry &g = jobs[c].g;
                 w = std::max<int64_t>(w, jobs[c].params.n_trials * (int64_t)(g.zstart[g.S] + g.M * g.M));
@@ -797,6 +816,28 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
         total_sites += (uint64_t)jobs[c].g.N;
         max_E = std::max(max_E, jobs[c].g.S * jobs[c].g.M * jobs[c].g.M);
     }
+    // A few long chains leave most of the chip idle, and a chain near its target
+    // rarely commits: such calls hand quiet chains' steps to the scan kernel
+    // (mc_kernels.hip), one round of scan and chain launches per commit that ends
+    // a quiet stretch.  The rounds of a call are launched without waiting; a round
+    // that finds nothing to do costs its launches only, and a call whose chains
+    // are not done after them goes on in further rounds (below).
+    int64_t longest = 0;
+    for (int c = 0; c < n; ++c) {
+        const int64_t B = jobs[c].params.cand_per_step;
+        longest = std::max(longest, (jobs[c].params.n_trials + B - 1) / B);
+    }
+    const bool wide = n <= kWideChains && longest >= kWideSteps;
+    const int rounds = !wide ? 0 : longest >= kManySteps ? kRoundsLong : kRoundsShort;
+    std::vector<size_t> o_image(n, 0), o_nulls(n, 0);
+    if (wide)
+        for (int c = 0; c < n; ++c) {
+            off = align256(off);
+            o_nulls[c] = off;
+            off = align256(off + kScanCap);
+            o_image[c] = off;
+            off += (size_t)species_store_bytes(shape[c].store, jobs[c].g.Npad);
+        }
     const uint32_t count_tile = count_tile_for(total_sites);
     std::vector<uint32_t> tile0v(n);
     for (int c = 0; c < n; ++c) {
@@ -811,7 +852,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     PYHEA_HIP(hipGetDevice(&dev));
     std::vector<int64_t> key = {dev, n, (int64_t)off, (int64_t)x_end, (int64_t)y_begin, (int64_t)y_end,
                                 (int64_t)o_descs, (int64_t)o_tasks, (int64_t)o_tile0, (int64_t)o_bad, n_tiles,
-                                count_tile, max_E};
+                                count_tile, max_E, rounds};
     for (const Launch &L : launches)
         key.insert(key.end(), {L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds});
     ChainPlan *plan = nullptr;
@@ -839,34 +880,67 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     };
     rebase(base);
 
+    // rounds of one launch group: the quiet chains' windows, then the chains
+    auto scan_rounds = [&](const Launch &L, int nr, hipStream_t ls) -> hipError_t {
+        // blocks that fill the chip: as many per CU as their LDS allows, 32 wavefronts at most
+        const int lds = scan_lds_bytes(L.S, L.M) + L.store_bytes;
+        const int per_cu = std::max(1, std::min(2048 / kScanThreads, lds_budget / std::max(lds, 1)));
+        const int blocks = std::max(1, cu_count() * per_cu / L.count);
+        for (int r = 0; r < nr; ++r) {
+            hipError_t e = launch_scan(ddev + L.first, L.count, L.store, L.M, L.store_bytes, L.S, blocks, ls);
+            if (e != hipSuccess) return e;
+            e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds, INT_MAX, ls,
+                          kQuietSteps);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    // the chains' launches, one per group, groups side by side on auxiliary streams
+    // (first: from the initial configurations; otherwise nr further rounds)
+    auto run_launches = [&](hipStream_t s, const hipStream_t *aux_set, bool first, int nr) -> hipError_t {
+        hipError_t e;
+        Fork fork;
+        if ((e = fork.begin(s, (int)launches.size(), aux_set)) != hipSuccess) return e;
+        for (size_t l = 0; l < launches.size(); ++l) {
+            const Launch &L = launches[l];
+            hipStream_t ls = fork.stream((int)l);
+            if (first) {
+                if (L.store == kStoreGlobal && (e = launch_pad_fill(ddev + L.first, L.count, ls)) != hipSuccess)
+                    return e;
+                if ((e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds,
+                                   INT_MAX, ls, wide ? kQuietSteps : 0)) != hipSuccess)
+                    return e;
+            }
+            if ((e = scan_rounds(L, nr, ls)) != hipSuccess) return e;
+            if (L.store == kStoreGlobal && (e = launch_pad_drain(ddev + L.first, L.count, ls)) != hipSuccess)
+                return e;
+        }
+        return fork.end();
+    };
+    // the states' final objective, and a fresh recount of every final configuration
+    auto finish = [&](hipStream_t s) -> hipError_t {
+        const hipError_t e = launch_final_objective(ddev, n, s);
+        if (e != hipSuccess) return e;
+        return launch_count_tasks(tasks + n, tile0, n, n_tiles, count_tile, max_E, s);
+    };
     // the device work after the upload: zeroed read-back block; initial pair counts
     // of every chain's configuration in one launch, then the ratio tables from
-    // them (an invalid chain is marked and skipped); the chains, one launch per
-    // group, groups side by side on auxiliary streams; the states' final
-    // objective; a fresh recount of every final configuration
+    // them (an invalid chain is marked and skipped); the chains; their results
     auto device_work = [&](hipStream_t s, const hipStream_t *aux_set) -> hipError_t {
         hipError_t e;
         if ((e = launch_zero_i32((int32_t *)base, (int64_t)(x_end / 4), s)) != hipSuccess) return e;
         if ((e = launch_count_tasks(tasks, tile0, n, n_tiles, count_tile, max_E, s)) != hipSuccess) return e;
         if ((e = launch_chain_ratio(ddev, n, (const int32_t *)(base + o_bad), s)) != hipSuccess) return e;
-        {
-            Fork fork;
-            if ((e = fork.begin(s, (int)launches.size(), aux_set)) != hipSuccess) return e;
-            for (size_t l = 0; l < launches.size(); ++l) {
-                const Launch &L = launches[l];
-                hipStream_t ls = fork.stream((int)l);
-                if (L.store == kStoreGlobal && (e = launch_pad_fill(ddev + L.first, L.count, ls)) != hipSuccess)
-                    return e;
-                if ((e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds,
-                                   INT_MAX, ls)) != hipSuccess)
-                    return e;
-                if (L.store == kStoreGlobal && (e = launch_pad_drain(ddev + L.first, L.count, ls)) != hipSuccess)
-                    return e;
-            }
-            if ((e = fork.end()) != hipSuccess) return e;
-        }
-        if ((e = launch_final_objective(ddev, n, s)) != hipSuccess) return e;
-        return launch_count_tasks(tasks + n, tile0, n, n_tiles, count_tile, max_E, s);
+        if ((e = run_launches(s, aux_set, true, rounds)) != hipSuccess) return e;
+        return finish(s);
+    };
+    // a call whose chains are not done yet: more rounds, and its results again
+    auto more_work = [&](hipStream_t s) -> hipError_t {
+        hipError_t e;
+        if ((e = run_launches(s, nullptr, false, kRoundsLong)) != hipSuccess) return e;
+        if ((e = launch_zero_i32((int32_t *)(base + o_recount), (int64_t)Etot, s)) != hipSuccess) return e;
+        if ((e = launch_zero_i32((int32_t *)(base + o_bad2), n, s)) != hipSuccess) return e;
+        return finish(s);
     };
     if (plan && !plan->exec) {
         if (plan->failed || record_plan(plan, device_work) != hipSuccess) {
@@ -915,6 +989,11 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
             d.log = j.log_dev;
             d.log_cap = j.log_dev ? j.log_cap : 0;
             d.state = (ChainState *)(base + o_state) + c;
+            if (wide) {
+                d.image = (uint8_t *)(base + o_image[c]);
+                d.scan_nulls = (uint8_t *)(base + o_nulls[c]);
+                d.scan_cap = kScanCap;
+            }
             d.store = shape[c].store;
             d.lds_bytes = shape[c].lds;
             d.sym = symmetric_target(j.target.data(), j.g.S, j.g.M);
@@ -941,12 +1020,17 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     } else {
         PYHEA_HIP(device_work(stream, nullptr));
     }
-    PYHEA_HIP(hipMemcpyAsync(hxp, base, x_end, hipMemcpyDeviceToHost, stream));
-    PYHEA_HIP(hipStreamSynchronize(stream));
+    const ChainState *sts = (const ChainState *)(hxp + o_state);
+    for (;;) {
+        PYHEA_HIP(hipMemcpyAsync(hxp, base, x_end, hipMemcpyDeviceToHost, stream));
+        PYHEA_HIP(hipStreamSynchronize(stream));
+        // every further set of rounds moves each unfinished chain on by at least a step
+        if (std::all_of(sts, sts + n, [](const ChainState &s) { return s.done != 0; })) break;
+        PYHEA_HIP(more_work(stream));
+    }
     lease.drained = true;
     const int32_t *cnt = (const int32_t *)(hxp + o_counts);
     const int32_t *rec = (const int32_t *)(hxp + o_recount);
-    const ChainState *sts = (const ChainState *)(hxp + o_state);
     if (final_counts) final_counts->assign(n, {});
     int first_invalid = -1;
     for (int c = 0; c < n; ++c) {
