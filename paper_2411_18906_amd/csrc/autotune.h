@@ -10,38 +10,30 @@
 namespace pyhea {
 
 // Launch shape of one chain: where its configuration lives (LDS bytes, LDS
-// nibbles or HBM), the wavefronts per slot group (W) and whether the offsets
-// are spread evenly over them (bal), and how many steps one pass evaluates
-// (K, 1..kMaxLookahead).
+// nibbles or HBM), the wavefronts of its workgroup (W), whether it scans quiet
+// steps in windows (K > 1) or step by step (K = 1), and how many members a commit
+// chunk holds (CH, 1..kChunk).
 struct LaunchShape {
     int store;
     int W;
-    int bal;
     int K;
-    int CH;   // speculative commit chunk (0: commits one by one)
+    int CH;
     int lds;
 };
 
-// Variants: 0 = automatic (of LDS bytes, LDS nibbles and HBM, the store whose
-// room for steps per pass gives the best measured rate; each wavefront gathers
-// its own shell's offsets); 1 = LDS nibbles or HBM, chosen the same way; 2 =
-// always HBM; 3 = the automatic shape (kept as an explicit
-// name); 4 = automatic store, every wavefront of a slot group gathers an equal
-// share of all offsets and the shells' partial histograms meet in LDS;
-// 5 = the automatic shape with DISJOINT commits decided one by one; 6 = the
-// automatic shape with speculative commit chunks of 4.  The block size follows the
-// number of chains launched together (n_chains) so that all can be resident;
-// the steps per pass are the largest (up to 8) that fit it and the store, unless
-// forced.
+// Variants: 0, 3, 4 = automatic (the first of LDS bytes, LDS nibbles and HBM in
+// which the chain fits); 1 = LDS nibbles or HBM; 2 = always HBM; 5 = the
+// automatic shape with commits decided one by one; 6 = with commit chunks of 4.
+// The block size follows the number of chains launched together (n_chains) so
+// that all can be resident.
 // Every variant gives bit-identical results.
 constexpr int kNumStoreVariants = 7;
 
 LaunchShape choose_launch(const Geometry &g, int B, int lds_budget, int variant, int n_chains);
 int wave_budget(int n_chains);
 
-// Candidate shapes for measurement: for each store that fits, the most steps
-// per pass the wave budget allows, about half of that and one step, each with
-// the largest commit chunk that fits and with commits one by one.
+// Candidate shapes for measurement: for each store that fits, quiet steps in
+// windows and step by step, with the largest commit chunk that fits.
 std::vector<LaunchShape> candidate_launches(const Geometry &g, int B, int lds_budget, int n_chains);
 // LDS bytes of shape s for a chain of geometry g (the species store depends on
 // the padded size).

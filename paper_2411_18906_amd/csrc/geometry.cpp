@@ -57,13 +57,6 @@ void offset_target(const Geometry &g, int b, int t, int dc[3], int *b_to) {
     *b_to = basis_of_parity(g.lattice, pos[0] & 1, pos[1] & 1, pos[2] & 1);
 }
 
-int32_t padded_delta(const Geometry &g, int b, int t) {
-    int dc[3], bt;
-    offset_target(g, b, t, dc, &bt);
-    const int64_t d = ((int64_t)dc[2] * g.P[1] + dc[1]) * g.P[0] + dc[0];
-    return (int32_t)(d * g.A + (bt - b));
-}
-
 namespace {
 pyhea_status build_geometry_uncached(const pyhea_lattice *lat, Geometry *g, std::string *err);
 }
@@ -181,8 +174,17 @@ pyhea_status build_geometry_uncached(const pyhea_lattice *lat, Geometry *g, std:
             for (int a = 0; a < 3; ++a) halo = std::max(halo, std::abs(dc[a]));
         }
     g->halo = std::max(halo, 1);
-    for (int a = 0; a < 3; ++a) g->P[a] = g->L[a] + 2 * g->halo;
-    g->Npad = (int64_t)g->A * g->P[0] * g->P[1] * g->P[2];
+    g->hh = g->lattice == PYHEA_FCC ? 2 : maxc;   // even for FCC: padded sums stay even
+    for (int a = 0; a < 3; ++a) g->P2[a] = 2 * g->L[a] + 2 * g->hh;
+    const int px = g->P2[0], py = g->P2[1];
+    if (g->lattice == PYHEA_FCC) {
+        g->B2 = px + 1;                              // px is even
+        g->A2 = (g->B2 * (py - 1) + px + 1) | 1;
+    } else {
+        g->B2 = px / 2;                              // rows of one parity lie two half units apart
+        g->A2 = 2 * (px / 2) * (py / 2) + g->B2 + 1;
+    }
+    g->Npad = ((int64_t)g->A2 * (g->P2[2] - 1) + (int64_t)g->B2 * (py - 1) + px - 1) / 2 + 1;
     return PYHEA_OK;
 }
 
@@ -197,10 +199,10 @@ void fill_chain_geometry(const Geometry &g, ChainDesc *d) {
     d->M = g.M;
     d->S = g.S;
     d->Z = g.Z;
-    d->halo = g.halo;
-    d->PX = g.P[0];
-    d->PY = g.P[1];
-    d->PZ = g.P[2];
+    d->hh = g.hh;
+    for (int a = 0; a < 3; ++a) d->P2[a] = g.P2[a];
+    d->A2 = g.A2;
+    d->B2 = g.B2;
     d->small_cell = g.small_cell;
     for (int k = 0; k < kMaxShells; ++k) {
         d->zk[k] = k < g.S ? g.z[k] : 0;
@@ -212,7 +214,7 @@ void fill_chain_geometry(const Geometry &g, ChainDesc *d) {
     d->inv_Lx = 1.0 / (double)g.L[0];
     d->inv_Ly = 1.0 / (double)g.L[1];
     std::memset(d->off, 0, sizeof(d->off));
-    std::memset(d->dlin, 0, sizeof(d->dlin));
+    std::memset(d->dl, 0, sizeof(d->dl));
     std::memset(d->off_mod, 0, sizeof(d->off_mod));
     for (int t = 0; t < g.Z; ++t) {
         int shell = 0;
@@ -227,7 +229,7 @@ void fill_chain_geometry(const Geometry &g, ChainDesc *d) {
             packed |= (((g.off[t][a] % m) + m) % m) << (10 * a);
         }
         d->off_mod[t] = packed;
-        for (int b = 0; b < g.A; ++b) d->dlin[b][t] = padded_delta(g, b, t);
+        d->dl[t] = (g.A2 * g.off[t][2] + g.B2 * g.off[t][1] + g.off[t][0]) / 2;   // exact: the sum is even
     }
 }
 

@@ -6,10 +6,10 @@
 // vectors of the k-th smallest length (squared radii FCC 2, 4, 6, 8 and BCC 3,
 // 4, 8, 11 in these units; coordination 12, 6, 24, 12 and 8, 6, 12, 24).
 //
-// Kernels never stream a neighbour list: each site id is turned into cell
-// coordinates and every neighbour is reached by adding a per-(basis, offset)
-// linear delta in a halo-padded copy of the configuration, so no modulo is
-// evaluated per neighbour.
+// Kernels never stream a neighbour list: the Monte Carlo kernels hold a
+// halo-padded copy of the configuration in which the index of a site is linear
+// in its half-unit coordinates, so that an offset is one delta for every site
+// and no modulo is evaluated per neighbour.
 #pragma once
 
 #include <stdint.h>
@@ -38,10 +38,16 @@ struct Geometry {
     int zstart[kMaxShells + 1] = {0};
     int8_t off[kMaxOffsets][3] = {};  // offsets, shell by shell
     int halo = 1;                    // largest |cell delta| of any (basis, offset)
+    int hh = 0;                      // halo of the padded copy, half units (>= any offset component)
     int small_cell = 0;              // some axis too short for the min-image shortcut
     int64_t N = 0;
-    int P[3] = {0, 0, 0};            // padded cells per axis (L + 2 halo)
-    int64_t Npad = 0;                // padded sites
+    // Padded copy: sites at (x, y, z) + hh, x < 2 L + 2 hh per axis, at index
+    // (A2 z + B2 y + x) / 2.  FCC (even coordinate sums) takes odd A2 and B2, BCC
+    // (equal parities) an odd sum A2 + B2, so the sum is even for every site; the
+    // strides are the smallest for which rows and layers do not overlap.
+    int P2[3] = {0, 0, 0};           // padded extent per axis, half units
+    int A2 = 0, B2 = 0;
+    int64_t Npad = 0;                // padded copy, sites
 };
 
 // Fills `g` from a descriptor.  Returns PYHEA_OK or PYHEA_EINVAL with a message.
@@ -52,9 +58,6 @@ void basis_vector(int lattice, int b, int out[3]);
 
 // Cell delta and target basis of offset t from basis b.
 void offset_target(const Geometry &g, int b, int t, int dc[3], int *b_to);
-
-// Linear delta in the padded layout for (basis b, offset t).
-int32_t padded_delta(const Geometry &g, int b, int t);
 
 // ---------------------------------------------------------------------------
 // Device descriptors
@@ -79,16 +82,17 @@ struct ChainState {
 };
 
 enum SpeciesStore : int32_t {
+    // one byte per site holds 5 times the species: the shift of its histogram field
     kStoreLds8 = 0,    // padded configuration in LDS, one byte per site
-    kStoreLds4 = 1,    // padded configuration in LDS, one nibble per site
-    kStoreGlobal = 2,  // padded configuration in HBM (one byte per site)
+    kStoreLds4 = 1,    // padded configuration in LDS, one nibble (the species) per site
+    kStoreGlobal = 2,  // padded configuration in HBM, one byte per site
 };
 
 // Everything one chain needs on the device.  Read-only for kernels except the
 // buffers it points to.
 struct ChainDesc {
     int32_t A, lgA, Lx, Ly, Lz, M, S, Z;
-    int32_t halo, PX, PY, PZ;
+    int32_t hh, P2[3], A2, B2;      // padded copy (Geometry)
     int32_t small_cell;
     int32_t zk[kMaxShells];
     int32_t zstart[kMaxShells + 1];
@@ -97,7 +101,7 @@ struct ChainDesc {
     uint32_t Npad;
     double inv_Lx, inv_Ly;          // 1/Lx, 1/Ly for exact small-integer division
     int8_t off[kMaxOffsets][4];     // dx, dy, dz, shell
-    int32_t dlin[4][kMaxOffsets];   // padded linear delta per (basis, offset)
+    int32_t dl[kMaxOffsets];        // delta of each offset in the padded copy
     int32_t off_mod[kMaxOffsets];   // offsets reduced mod the box, packed 10 bits/axis
     uint64_t seed;
     uint32_t chain_id;
@@ -109,7 +113,7 @@ struct ChainDesc {
     double w[kMaxShells];
     int8_t *species;       // [N] unpadded configuration, in/out
     int8_t *pad_global;    // [Npad] padded copy when store == kStoreGlobal
-    uint8_t *image;        // the LDS store of a chain that has gone quiet (16-byte aligned), or null
+    uint8_t *image;        // padded copy of a chain in LDS that has gone quiet (16-byte aligned), or null
     uint8_t *scan_nulls;   // [scan_cap] null draws per slot group of a scanned window, or null
     int32_t scan_cap;      // slot groups a scanned window may hold
     const double *R;       // [S][M][M]

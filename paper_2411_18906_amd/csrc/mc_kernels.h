@@ -7,30 +7,16 @@
 
 namespace pyhea {
 
-// LDS layout of the MC kernel (must match the carve order in mc_kernels.hip).
-// W = wavefronts per slot group (>= S), bal = offsets spread evenly over them
-// (partial histograms exchanged through LDS), K = steps whose candidates one
-// pass evaluates (records for K * B slots), CH = members of the conflict-free
-// set the speculative commit phase evaluates together (0: one by one; <= 16).
-__host__ __device__ inline int mc_lds_bytes(int S, int M, int B, int W = 0, int bal = 0, int K = 1, int CH = 0) {
-    auto r = [](int b) { return (b + 15) & ~15; };
-    const int E = S * M * M;
-    const int Bt = K * B;
-    int n = 0;
-    n += r(E * 32);                               // entry records
-    n += r(kMaxOffsets * 16) + r(kMaxOffsets * 4);     // dlin4, offmod
-    n += r(Bt * 8) + 3 * r(Bt * 4);               // rec_dS, pp, pq, ab
-    n += 2 * r(S * Bt * (M > 6 ? 8 : 4));         // rec_cp, rec_cq (histograms)
-    n += r(S * Bt * 8);                           // rec_dQ
-    n += 2 * r(Bt * 4);                           // order, list (per step of a pass)
-    n += r(2 * kMaxShells * 8) + r(32 * 4);       // sh_dQ (two buffers), sh_int
-    if (bal) n += r(S * W * 2 * Bt * (M > 6 ? 8 : 4));  // partial histograms
-    if (CH > 0) n += r(64 * 8) + r(CH * E * 8) + r(CH * E * 4) + r(16 * kMaxShells * 8) + r(16 * 4) + r(4 * 4);
-    return n;
-}
+constexpr int kMaxLookahead = 8;   // pyhea_tune_force_lookahead: 1 = step by step, more = quiet steps in windows
+constexpr int kRing = 8;           // steps whose candidates are drawn ahead
+constexpr int kChunk = 32;         // members of a commit chunk at most (half a wavefront)
+constexpr int kMaxWaves = 8;       // wavefronts of a chain's workgroup at most
+
+// LDS of the MC kernel without the species store: CH = members of a commit chunk.
+int mc_lds_bytes(int S, int M, int B, int CH);
 
 // bytes of the species store for a padded chain
-__host__ __device__ inline int64_t species_store_bytes(int store, int64_t Npad) {
+inline int64_t species_store_bytes(int store, int64_t Npad) {
     if (store == kStoreLds8) return (Npad + 15) & ~int64_t(15);
     if (store == kStoreLds4) return (((Npad + 7) / 8) * 4 + 15) & ~int64_t(15);
     return 0;
@@ -40,22 +26,17 @@ __host__ __device__ inline int64_t species_store_bytes(int store, int64_t Npad) 
 // device; remembers what it set, so repeated launches make no runtime call.
 hipError_t set_max_lds(const void *fn, size_t lds);
 
-// Wavefronts of one chain's block: K steps x slot groups x W.
-inline int mc_block_waves(int B, int W, int K) { return K * ((B + 63) / 64) * W; }
-int mc_block_threads(int B, int W, int K);
-constexpr int kMaxLookahead = 8;
-
 // One launch of n_chains chains (one block each) for up to max_steps steps.
 // quiet > 0 (chains with image or pad_global, scan_nulls and scan_cap set): a
 // chain also ends its launch, with a window to scan, once `quiet` steps in a row
 // committed nothing.
-hipError_t launch_mc(const ChainDesc *descs_dev, int n_chains, int store, int M, int S, int B, int W, int bal,
-                     int K, int CH, int lds_bytes, int max_steps, hipStream_t stream, int quiet = 0);
+hipError_t launch_mc(const ChainDesc *descs_dev, int n_chains, int store, int M, int B, int waves, int K, int CH,
+                     int lds_bytes, int max_steps, hipStream_t stream, int quiet = 0);
 
 // The windows of quiet chains (chains without one are skipped), each by
 // blocks_per_chain blocks; store_bytes: the largest LDS store of the chains.
 constexpr int kScanThreads = 512;
-inline int scan_lds_bytes(int S, int M) { return S * M * M * 32 + kMaxOffsets * 16; }
+int scan_lds_bytes(int S, int M);
 hipError_t launch_scan(const ChainDesc *descs_dev, int n_chains, int store, int M, int store_bytes, int S,
                        int blocks_per_chain, hipStream_t stream);
 // Ratio tables of chains from their initial counts (descriptor order; bad [n]

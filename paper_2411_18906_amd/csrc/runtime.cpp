@@ -373,8 +373,7 @@ pyhea_status probe_launch(const ChainJob &j, int n_chains, int lds_budget, const
     std::vector<LaunchShape> cand = candidate_launches(g, B, lds_budget, n_chains);
     int im = -1;
     for (int i = 0; i < (int)cand.size(); ++i)
-        if (cand[i].store == model.store && cand[i].W == model.W && cand[i].bal == model.bal && cand[i].K == model.K &&
-            cand[i].CH == model.CH)
+        if (cand[i].store == model.store && cand[i].W == model.W && cand[i].K == model.K && cand[i].CH == model.CH)
             im = i;
     if (im < 0) {
         cand.insert(cand.begin(), model);
@@ -478,7 +477,7 @@ pyhea_status probe_launch(const ChainJob &j, int n_chains, int lds_budget, const
         const LaunchShape &c = cand[i];
         hipError_t e = hipSuccess;
         if (c.store == kStoreGlobal && (e = launch_pad_fill(ddev + i, 1, stream)) != hipSuccess) return e;
-        e = launch_mc(ddev + i, 1, c.store, g.M, g.S, B, c.W, c.bal, c.K, c.CH, c.lds, steps, stream);
+        e = launch_mc(ddev + i, 1, c.store, g.M, B, c.W, c.K, c.CH, c.lds, steps, stream);
         if (e == hipSuccess && c.store == kStoreGlobal) e = launch_pad_drain(ddev + i, 1, stream);
         return e;
     };
@@ -729,10 +728,9 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     if (measure) {
         // (Written for groups: chains that share a launch under the cost model
         // would keep sharing one, the group's longest chain measured for all.)
-        std::map<std::tuple<int, int, int, int, int, int>, std::vector<int>> fam;
+        std::map<std::tuple<int, int, int, int, int>, std::vector<int>> fam;
         for (int c = 0; c < n; ++c)
-            fam[{shape[c].store, jobs[c].g.M, jobs[c].g.S, jobs[c].params.cand_per_step, shape[c].W, shape[c].bal}]
-                .push_back(c);
+            fam[{shape[c].store, jobs[c].g.M, jobs[c].g.S, jobs[c].params.cand_per_step, shape[c].W}].push_back(c);
         for (auto &kv : fam) {
             const std::vector<int> &members = kv.second;
             int rep = members[0];
@@ -750,7 +748,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
                 if (ok) record_tuned_launch(key, t, us);
                 have = ok;
             }
-            if (!have || t.W != jobs[rep].g.S) continue;
+            if (!have) continue;
             bool fits = true;
             for (int c : members) fits = fits && launch_lds_bytes(jobs[c].g, B, t) <= lds_budget;
             if (!fits) continue;
@@ -773,15 +771,15 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     // launch whose longest chain is longest (per-trial cost taken as offsets
     // gathered plus count entries evaluated) goes first, so it starts first
     struct Launch {
-        int first, count, store, M, S, B, W, bal, K, CH, lds, store_bytes;
+        int first, count, store, M, S, B, W, K, CH, lds, store_bytes;
     };
     std::vector<Launch> launches;
     std::vector<int> pos(n);   // descriptor position of each chain
     {
-        std::map<std::tuple<int, int, int, int, int, int, int, int>, std::vector<int>> groups;
+        std::map<std::tuple<int, int, int, int, int, int, int>, std::vector<int>> groups;
         for (int c = 0; c < n; ++c)
-            groups[{shape[c].store, jobs[c].g.M, jobs[c].g.S, jobs[c].params.cand_per_step, shape[c].W, shape[c].bal,
-                    shape[c].K, shape[c].CH}]
+            groups[{shape[c].store, jobs[c].g.M, jobs[c].g.S, jobs[c].params.cand_per_step, shape[c].W, shape[c].K,
+                    shape[c].CH}]
                 .push_back(c);
         int at = 0;
         std::vector<std::pair<int64_t, Launch>> byw;
@@ -792,7 +790,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
             });
             Launch L{at, (int)idx.size(), std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first),
                      std::get<3>(kv.first), std::get<4>(kv.first), std::get<5>(kv.first), std::get<6>(kv.first),
-                     std::get<7>(kv.first), 0, 0};
+                     0, 0};
             int64_t w = 0;
             for (int c : idx) {
                 L.lds = std::max(L.lds, shape[c].lds);
@@ -836,7 +834,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
             o_nulls[c] = off;
             off = align256(off + kScanCap);
             o_image[c] = off;
-            off += (size_t)species_store_bytes(shape[c].store, jobs[c].g.Npad);
+            if (shape[c].store != kStoreGlobal) off += align256((size_t)jobs[c].g.Npad);
         }
     const uint32_t count_tile = count_tile_for(total_sites);
     std::vector<uint32_t> tile0v(n);
@@ -854,7 +852,7 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
                                 (int64_t)o_descs, (int64_t)o_tasks, (int64_t)o_tile0, (int64_t)o_bad, n_tiles,
                                 count_tile, max_E, rounds};
     for (const Launch &L : launches)
-        key.insert(key.end(), {L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds});
+        key.insert(key.end(), {L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.K, L.CH, L.lds});
     ChainPlan *plan = nullptr;
     if (graphs_enabled()) PYHEA_HIP(chain_plan(key, off, &plan));
     std::unique_lock<std::mutex> plan_lock;
@@ -883,14 +881,13 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     // rounds of one launch group: the quiet chains' windows, then the chains
     auto scan_rounds = [&](const Launch &L, int nr, hipStream_t ls) -> hipError_t {
         // blocks that fill the chip: as many per CU as their LDS allows, 32 wavefronts at most
-        const int lds = scan_lds_bytes(L.S, L.M) + L.store_bytes;
+        const int lds = scan_lds_bytes(L.S, L.M) + (L.store == kStoreLds8 ? L.store_bytes : 0);
         const int per_cu = std::max(1, std::min(2048 / kScanThreads, lds_budget / std::max(lds, 1)));
         const int blocks = std::max(1, cu_count() * per_cu / L.count);
         for (int r = 0; r < nr; ++r) {
             hipError_t e = launch_scan(ddev + L.first, L.count, L.store, L.M, L.store_bytes, L.S, blocks, ls);
             if (e != hipSuccess) return e;
-            e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds, INT_MAX, ls,
-                          kQuietSteps);
+            e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.B, L.W, L.K, L.CH, L.lds, INT_MAX, ls, kQuietSteps);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -907,8 +904,8 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
             if (first) {
                 if (L.store == kStoreGlobal && (e = launch_pad_fill(ddev + L.first, L.count, ls)) != hipSuccess)
                     return e;
-                if ((e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.S, L.B, L.W, L.bal, L.K, L.CH, L.lds,
-                                   INT_MAX, ls, wide ? kQuietSteps : 0)) != hipSuccess)
+                if ((e = launch_mc(ddev + L.first, L.count, L.store, L.M, L.B, L.W, L.K, L.CH, L.lds, INT_MAX, ls,
+                                   wide ? kQuietSteps : 0)) != hipSuccess)
                     return e;
             }
             if ((e = scan_rounds(L, nr, ls)) != hipSuccess) return e;

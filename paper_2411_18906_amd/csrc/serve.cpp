@@ -101,7 +101,7 @@ struct Job {
     ChainDesc desc{};
     int store = kStoreLds8;
     int lds = 0;
-    int W = 1, bal = 0, K = 1, CH = 0;
+    int W = 1, K = 1, CH = 1;
     int shape_measured = 0;
     JobLayout lay{};
 };
@@ -117,7 +117,7 @@ constexpr int kServeStreams = 16;
 constexpr int kMaxStepScale = 16;
 
 // The launch shape of a group of resident jobs (one persistent launch each round).
-using GroupKey = std::tuple<int, int, int, int, int, int, int, int>;
+using GroupKey = std::tuple<int, int, int, int, int, int, int>;
 
 struct Server {
     int device = 0;
@@ -386,7 +386,7 @@ void Server::run() {
         // one round: group by launch shape, one stream per group
         std::map<GroupKey, std::vector<Job *>> groups;
         for (Job *j : run_set)
-            groups[{j->store, j->g.M, j->g.S, j->params.cand_per_step, j->W, j->bal, j->K, j->CH}].push_back(j);
+            groups[{j->store, j->g.M, j->g.S, j->params.cand_per_step, j->W, j->K, j->CH}].push_back(j);
         std::vector<ChainDesc> descs;
         std::vector<Job *> order;
         std::vector<std::pair<size_t, std::vector<Job *>>> launches;
@@ -437,8 +437,7 @@ void Server::run() {
             ok = s == s0 || hipStreamWaitEvent(s, ready, 0) == hipSuccess;
             if (timed) ok = ok && hipEventRecord(events[2 * gi], s) == hipSuccess;
             ok = ok && launch_mc((const ChainDesc *)desc_dev + L.first, (int)L.second.size(), j0->store, j0->g.M,
-                                 j0->g.S, j0->params.cand_per_step, j0->W, j0->bal, j0->K, j0->CH, lds,
-                                 steps[gi], s) == hipSuccess;
+                                 j0->params.cand_per_step, j0->W, j0->K, j0->CH, lds, steps[gi], s) == hipSuccess;
             if (timed) ok = ok && hipEventRecord(events[2 * gi + 1], s) == hipSuccess;
         }
         for (size_t i = 0; i < streams.size(); ++i) ok = ok && hipStreamSynchronize(streams[i]) == hipSuccess;
@@ -614,7 +613,7 @@ pyhea_status pyhea_serve_submit(void *server, uint64_t job_id, const pyhea_latti
     LaunchShape t;
     if (measure_enabled() && tuned_launch(tune_key(g, params->cand_per_step, s->max_slots), &t)) {
         t.lds = (int)launch_lds_bytes(g, params->cand_per_step, t);
-        if (t.lds <= s->lds_budget && t.W == g.S) {
+        if (t.lds <= s->lds_budget) {
             ls = t;
             j->shape_measured = 1;
         }
@@ -622,7 +621,6 @@ pyhea_status pyhea_serve_submit(void *server, uint64_t job_id, const pyhea_latti
     j->store = ls.store;
     j->lds = ls.lds;
     j->W = ls.W;
-    j->bal = ls.bal;
     j->CH = ls.CH;
     j->K = ls.K;
     j->footprint = job_footprint(g, j->store);
