@@ -422,8 +422,9 @@ pyhea_status pyhea_tune_measure(int32_t on);
  * depend on this.  on = 0 runs every call eagerly. */
 pyhea_status pyhea_tune_graphs(int32_t on);
 
-/* Full-evaluation kernel: -1 = automatic (bit-sliced where it covers the
- * geometry, else gather), 0 = gather, 1 = bit-sliced where possible (a
+/* Full-evaluation kernel: -1 = automatic (on the matrix cores where they are
+ * the faster way, most of 4 and 5 species; else bit-sliced where that covers
+ * the geometry, else gather), 0 = gather, 1 = bit-sliced where possible (a
  * configuration whose layers would take more than half of a CU's LDS is cut
  * along z so that two workgroups share each CU), 2 = bit-sliced without that
  * cut, 3 = bit-sliced cut for four workgroups per CU, 4 = streaming where it

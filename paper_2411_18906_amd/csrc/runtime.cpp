@@ -13,6 +13,7 @@
 
 #include "autotune.h"
 #include "sro_bits.h"
+#include "sro_mfma.h"
 
 namespace pyhea {
 
@@ -164,9 +165,18 @@ bool stream_shape(const Geometry &g, int64_t K, StreamDesc *sd) {
 }
 }  // namespace
 
+namespace {
+// the matrix-core kernel's launch shape for K configurations of g (false: not taken)
+bool mfma_shape(const Geometry &g, int64_t K, MfmaDesc *md) {
+    return forced_eval_kernel() < 0 && fill_mfma_desc(g, max_lds_per_block(), K, md);
+}
+}  // namespace
+
 size_t count_partial_bytes(const Geometry &g, int64_t K) {
     BitDesc bd;
     StreamDesc sd;
+    MfmaDesc md;
+    if (K > 0 && mfma_shape(g, K, &md)) return mfma_partial_bytes(md, K);
     if (K <= 0 || stream_shape(g, K, &sd) || !bit_shape(g, K, &bd) || bd.nchunks <= 1) return 0;
     return (size_t)K * bd.nchunks * bd.partial_stride * 4;
 }
@@ -176,6 +186,19 @@ pyhea_status count_configs(const Geometry &g, int64_t K, const int8_t *species, 
                            void *partial_scratch) {
     if (fused) *fused = false;
     if (K <= 0) return PYHEA_OK;
+    MfmaDesc md;
+    if (mfma_shape(g, K, &md)) {
+        void *partial = partial_scratch;
+        const bool own = partial == nullptr && md.nchunks > 1;
+        if (own) PYHEA_HIP(pool_alloc(&partial, mfma_partial_bytes(md, K), stream));
+        const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
+        const hipError_t e = launch_count_mfma(md, K, species, (int32_t *)partial, counts, bad, fuse ? tw : nullptr,
+                                               fuse ? S_F : nullptr, stream);
+        if (own) (void)hipFreeAsync(partial, stream);
+        PYHEA_HIP(e);
+        if (fused) *fused = fuse;
+        return PYHEA_OK;
+    }
     StreamDesc sd;
     if (stream_shape(g, K, &sd)) {
         const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
