@@ -290,33 +290,33 @@ pyhea_status pyhea_trial_eval(const pyhea_lattice *lat, const pyhea_objective *o
     }
     hipStream_t stream = as_stream(stream_);
     const int E = g.S * g.M * g.M;
+    // device block: bad | counts [E] | sums of the counting
+    const size_t o_part = 256 + (((size_t)E * 4 + 255) & ~size_t(255));
+    const size_t part = count_partial_bytes(g, 1);
     AsyncBuffer buf;
     buf.stream = stream;
-    PYHEA_HIP(pool_alloc(&buf.ptr, 256 + E * 4 + (E + kMaxShells) * 8 + 256, stream));
+    PinnedLease lease;   // (given back after the stream has drained)
+    PYHEA_HIP(pinned_lease(64, stream, &lease));
+    volatile int32_t *status = (volatile int32_t *)lease.b.p;
+    PYHEA_HIP(pool_alloc(&buf.ptr, o_part + part, stream));
     int32_t *bad = (int32_t *)buf.ptr;
     int32_t *counts = (int32_t *)((char *)buf.ptr + 256);
-    double *tdev = (double *)((char *)buf.ptr + 256 + ((E * 4 + 255) & ~255));
+    s = count_configs(g, 1, species_dev, counts, bad, stream, nullptr, nullptr, nullptr,
+                      part ? (char *)buf.ptr + o_part : nullptr);
+    if (s != PYHEA_OK) return s;
     EvalDesc ed;
     fill_eval_desc(g, &ed);
-    PYHEA_HIP(launch_count_gather(ed, 1, species_dev, counts, bad, stream));
-    std::vector<int32_t> c32(E);
-    int32_t badh = 0;
-    PYHEA_HIP(hipMemcpyAsync(c32.data(), counts, E * 4, hipMemcpyDeviceToHost, stream));
-    PYHEA_HIP(hipMemcpyAsync(&badh, bad, 4, hipMemcpyDeviceToHost, stream));
+    SmallTable tw{};
+    std::memcpy(tw.v, obj->target, E * 8);
+    std::memcpy(tw.v + E, obj->weight, g.S * 8);
+    PYHEA_HIP(launch_trial_eval(ed, tw, species_dev, counts, bad, n_pairs, pairs_dev, dS_dev, dN_dev,
+                                (int32_t *)lease.b.p, stream));
     PYHEA_HIP(hipStreamSynchronize(stream));
-    std::vector<int64_t> c64(c32.begin(), c32.end());
-    int64_t n[kMaxSpecies];
-    if (badh || !species_totals(g, c64.data(), n)) {
+    lease.drained = true;
+    if (*status != 0) {
         set_error("species ids must lie in [0, n_species) and every species must occur");
         return PYHEA_EINVAL;
     }
-    std::vector<double> tw(E + kMaxShells, 0.0);
-    std::memcpy(tw.data(), obj->target, E * 8);
-    std::memcpy(tw.data() + E, obj->weight, g.S * 8);
-    PYHEA_HIP(hipMemcpyAsync(tdev, tw.data(), tw.size() * 8, hipMemcpyHostToDevice, stream));
-    PYHEA_HIP(launch_trial_eval(ed, species_dev, counts, tdev, tdev + E, n_pairs, pairs_dev, dS_dev, dN_dev,
-                                stream));
-    PYHEA_HIP(hipStreamSynchronize(stream));
     return guard(PYHEA_OK);
 }
 

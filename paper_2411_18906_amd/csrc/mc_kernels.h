@@ -104,9 +104,11 @@ hipError_t launch_count_gather(const EvalDesc &ed, int64_t K, const int8_t *spec
 hipError_t launch_objective_epilogue(const EvalDesc &ed, int64_t K, const int32_t *counts,
                                      const int32_t *bad, const double *target, const double *weight,
                                      double *S_F, double *alpha, hipStream_t stream);
-hipError_t launch_trial_eval(const EvalDesc &ed, const int8_t *species, const int32_t *counts,
-                             const double *target, const double *weight, int64_t n_pairs,
-                             const int32_t *pairs, double *dS, int32_t *dN, hipStream_t stream);
+// `status` is host memory: 1 if an id is invalid or a species absent (nothing else is
+// written then), else 0.
+hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,
+                             const int32_t *bad, int64_t n_pairs, const int32_t *pairs, double *dS, int32_t *dN,
+                             int32_t *status, hipStream_t stream);
 // Non-incremental baseline: out[i] = base with sites pairs[i] swapped (out
 // [n][N]); *bad |= 1 for a pair outside [0, N).  dS[i] = S_F[i][0] - S0[0].
 hipError_t launch_swap_copies(const int8_t *base, int64_t N, const int32_t *pairs, int n, int8_t *out, int32_t *bad,

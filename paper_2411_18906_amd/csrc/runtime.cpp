@@ -46,6 +46,38 @@ hipError_t pool_alloc(void **ptr, size_t bytes, hipStream_t stream) {
     return hipMallocAsync(ptr, bytes, stream);
 }
 
+namespace {
+std::mutex g_pin_mu;
+auto *g_pin_free = new std::vector<PinnedBuf>();
+}  // namespace
+
+PinnedLease::~PinnedLease() {
+    if (!b.p) return;
+    if (!drained) (void)hipStreamSynchronize(stream);
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    g_pin_free->push_back(b);
+}
+
+hipError_t pinned_lease(size_t bytes, hipStream_t stream, PinnedLease *out) {
+    out->stream = stream;
+    {
+        std::lock_guard<std::mutex> lock(g_pin_mu);
+        for (size_t i = 0; i < g_pin_free->size(); ++i)
+            if ((*g_pin_free)[i].cap >= bytes) {
+                out->b = (*g_pin_free)[i];
+                g_pin_free->erase(g_pin_free->begin() + (long)i);
+                return hipSuccess;
+            }
+    }
+    const size_t cap = std::max<size_t>((bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1), size_t(1) << 20);
+    void *p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, cap, hipHostMallocDefault);
+    if (e != hipSuccess) return e;
+    out->b.p = (char *)p;
+    out->b.cap = cap;
+    return hipSuccess;
+}
+
 hipError_t set_max_lds(const void *fn, size_t lds) {
     static std::mutex mu;
     static std::map<std::pair<int, const void *>, size_t> done;
@@ -557,50 +589,6 @@ pyhea_status probe_launch(const ChainJob &j, int n_chains, int lds_budget, const
 }  // namespace
 
 namespace {
-
-// Page-locked host staging for a chain call's upload and read-back: copies
-// from and to it are single DMA transfers, and the upload returns at once.
-// Buffers are leased from a pool and kept until exit.  A lease is returned
-// only after its stream has drained, so no copy still reads or writes a
-// buffer the next call fills.
-struct PinnedBuf {
-    char *p = nullptr;
-    size_t cap = 0;
-};
-std::mutex g_pin_mu;
-auto *g_pin_free = new std::vector<PinnedBuf>();
-
-struct PinnedLease {
-    PinnedBuf b;
-    hipStream_t stream = nullptr;
-    bool drained = false;
-    ~PinnedLease() {
-        if (!b.p) return;
-        if (!drained) (void)hipStreamSynchronize(stream);
-        std::lock_guard<std::mutex> lock(g_pin_mu);
-        g_pin_free->push_back(b);
-    }
-};
-
-hipError_t pinned_lease(size_t bytes, hipStream_t stream, PinnedLease *out) {
-    out->stream = stream;
-    {
-        std::lock_guard<std::mutex> lock(g_pin_mu);
-        for (size_t i = 0; i < g_pin_free->size(); ++i)
-            if ((*g_pin_free)[i].cap >= bytes) {
-                out->b = (*g_pin_free)[i];
-                g_pin_free->erase(g_pin_free->begin() + (long)i);
-                return hipSuccess;
-            }
-    }
-    const size_t cap = std::max<size_t>((bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1), size_t(1) << 20);
-    void *p = nullptr;
-    const hipError_t e = hipHostMalloc(&p, cap, hipHostMallocDefault);
-    if (e != hipSuccess) return e;
-    out->b.p = (char *)p;
-    out->b.cap = cap;
-    return hipSuccess;
-}
 
 // Recorded device work of chain calls: a persistent arena and the graph that
 // runs a call's launches on it (run_chains).  A structure is recorded the

@@ -26,6 +26,23 @@ pyhea_status device_error(hipError_t e, const char *what);
 constexpr uint64_t kPoolRetainBytes = uint64_t(2) << 30;
 hipError_t pool_alloc(void **ptr, size_t bytes, hipStream_t stream);
 
+// Page-locked host memory of a call: staging for its upload and read-back (copies from
+// and to it are single DMA transfers, and the upload returns at once), or results that a
+// kernel writes there itself.  Buffers are leased from a pool and kept until exit.  A
+// lease is returned only after its stream has drained, so no copy or kernel still reads or
+// writes a buffer the next call fills.
+struct PinnedBuf {
+    char *p = nullptr;
+    size_t cap = 0;
+};
+struct PinnedLease {
+    PinnedBuf b;
+    hipStream_t stream = nullptr;
+    bool drained = false;
+    ~PinnedLease();
+};
+hipError_t pinned_lease(size_t bytes, hipStream_t stream, PinnedLease *out);
+
 // Largest dynamic LDS one workgroup may allocate on the current device.
 int max_lds_per_block();
 

@@ -322,79 +322,116 @@ __device__ __forceinline__ int32_t site_at(const EvalDesc &ed, int x, int y, int
     return (((z >> 1) * ed.Ly + (y >> 1)) * ed.Lx + (x >> 1)) * ed.A + b;
 }
 
-// dS and dN of given swaps against one configuration (no swap applied).
-__global__ void trial_eval_kernel(EvalDesc ed, const int8_t *__restrict__ sp,
-                                  const int32_t *__restrict__ counts, const double *__restrict__ target,
-                                  const double *__restrict__ weight, int64_t n_pairs,
-                                  const int32_t *__restrict__ pairs, double *__restrict__ dS_out,
-                                  int32_t *__restrict__ dN_out) {
-    const int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (u >= n_pairs) return;
+// dS and dN of given swaps against one configuration (no swap applied).  Half a
+// wavefront takes a pair: its lanes read the neighbours of both sites at once and add up
+// the change of the rows of species a and b in LDS; then a lane per row of a shell sums its
+// M terms and one lane the rows, in the order of Eq. 3.  What no swap changes (R, the old
+// terms) is made once per workgroup.  A lane per pair took 83 us for 4,096 pairs on FCC
+// 20^3, 5 species, 3 shells: 42 dependent reads twice, row counters in scratch memory and
+// 75 divisions per pair; now the call, count included, takes 59 us of 273.  Bound by the
+// latency of those steps and the launches.
+// *status (host memory): 1 if an id is invalid or a species absent, and nothing else is
+// written then.
+constexpr int kTrialLanes = 32;      // a lane for each of S M rows
+constexpr int kTrialThreads = 256;
+__global__ void __launch_bounds__(kTrialThreads)
+trial_eval_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, const int32_t *__restrict__ counts,
+                  const int32_t *__restrict__ bad, int64_t n_pairs, const int32_t *__restrict__ pairs,
+                  double *__restrict__ dS_out, int32_t *__restrict__ dN_out, int32_t *__restrict__ status) {
+    constexpr int kGroups = kTrialThreads / kTrialLanes, kMaxE = kMaxShells * kMaxSpecies * kMaxSpecies;
+    __shared__ int64_t n[kMaxSpecies];
+    __shared__ int32_t off[kMaxOffsets], cnt[kMaxE];
+    __shared__ double R[kMaxE], t[kMaxE], old_sq[kMaxE], weight[kMaxShells];
+    __shared__ int32_t D_all[kGroups][kMaxShells][kMaxSpecies];
+    __shared__ double row_all[kGroups][kMaxShells * kMaxSpecies];
     const int M = ed.M, E = ed.S * M * M;
-    const int32_t p = pairs[2 * u], q = pairs[2 * u + 1];
-    if (p < 0 || q < 0 || (uint32_t)p >= ed.N || (uint32_t)q >= ed.N) {
-        dS_out[u] = __longlong_as_double(0x7ff8000000000000ll);
-        return;
-    }
-    const int a = sp[p], b = sp[q];
-    int64_t n[kMaxSpecies];
-    for (int i = 0; i < M; ++i) {
+    const int tid = (int)threadIdx.x;
+    if (tid < M) {
         int64_t r = 0;
-        for (int j = 0; j < M; ++j) r += counts[i * M + j];
-        n[i] = r / ed.z0;
+        for (int j = 0; j < M; ++j) r += counts[tid * M + j];
+        n[tid] = r / ed.z0;
     }
-    int pp[3], pq[3];
-    {
-        const SiteCoord c = site_coord((uint32_t)p, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
-        int bx, by, bz;
-        basis_bits(ed.A, c.b, bx, by, bz);
-        pp[0] = 2 * c.cx + bx;
-        pp[1] = 2 * c.cy + by;
-        pp[2] = 2 * c.cz + bz;
-        const SiteCoord d = site_coord((uint32_t)q, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
-        basis_bits(ed.A, d.b, bx, by, bz);
-        pq[0] = 2 * d.cx + bx;
-        pq[1] = 2 * d.cy + by;
-        pq[2] = 2 * d.cz + bz;
+    for (int i = tid; i < ed.Z; i += kTrialThreads) __builtin_memcpy(&off[i], ed.off[i], 4);
+    if (tid < ed.S) weight[tid] = tw.v[E + tid];
+    __syncthreads();
+    bool ok = *bad == 0;
+    for (int i = 0; i < M; ++i) ok = ok && n[i] > 0;
+    if (blockIdx.x == 0 && tid == 0) *status = ok ? 0 : 1;
+    if (!ok) return;
+    for (int e = tid; e < E; e += kTrialThreads) {
+        const int k = e / (M * M), i = (e / M) % M, j = e % M;
+        cnt[e] = counts[e];
+        t[e] = tw.v[e];
+        R[e] = (double)ed.N / (double)(n[i] * n[j] * (int64_t)ed.zk[k]);
+        const double a0 = 1.0 - (double)counts[e] * R[e];
+        const double d0 = a0 - tw.v[e];
+        old_sq[e] = d0 * d0;
     }
-    double acc = 0.0;
-    for (int k = 0; k < ed.S; ++k) {
-        int D[kMaxSpecies];
-        for (int j = 0; j < M; ++j) D[j] = 0;
-        if (a != b) {
-            for (int t = 0; t < ed.Z; ++t) {
-                if (ed.off[t][3] != k) continue;
-                const int32_t rp = site_at(ed, pp[0] + ed.off[t][0], pp[1] + ed.off[t][1], pp[2] + ed.off[t][2]);
-                const int32_t rq = site_at(ed, pq[0] + ed.off[t][0], pq[1] + ed.off[t][1], pq[2] + ed.off[t][2]);
-                if (rp != q) D[sp[rp]] -= 1;
-                if (rq != p) D[sp[rq]] += 1;
+    __syncthreads();
+    const int group = tid / kTrialLanes, lane = tid % kTrialLanes;
+    int32_t(&D)[kMaxShells][kMaxSpecies] = D_all[group];
+    double *row = row_all[group];
+    // every group of a workgroup makes the same number of turns, for the barriers
+    for (int64_t u0 = (int64_t)blockIdx.x * kGroups; u0 < n_pairs; u0 += (int64_t)gridDim.x * kGroups) {
+        const int64_t u = u0 + group;
+        const bool here = u < n_pairs;
+        const int32_t p = here ? pairs[2 * u] : -1, q = here ? pairs[2 * u + 1] : -1;
+        const bool valid = here && p >= 0 && q >= 0 && (uint32_t)p < ed.N && (uint32_t)q < ed.N;
+        (&D[0][0])[lane] = 0;
+        __syncthreads();
+        int a = 0, b = 0;
+        if (valid) {
+            a = sp[p];
+            b = sp[q];
+            if (a != b) {
+                const SiteCoord c = site_coord((uint32_t)p, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
+                const SiteCoord d = site_coord((uint32_t)q, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
+                int bx, by, bz, ex, ey, ez;
+                basis_bits(ed.A, c.b, bx, by, bz);
+                basis_bits(ed.A, d.b, ex, ey, ez);
+                for (int i = lane; i < ed.Z; i += kTrialLanes) {
+                    const int32_t o = off[i];
+                    const int ox = (int8_t)o, oy = (int8_t)(o >> 8), oz = (int8_t)(o >> 16), k = o >> 24;
+                    const int32_t rp = site_at(ed, 2 * c.cx + bx + ox, 2 * c.cy + by + oy, 2 * c.cz + bz + oz);
+                    const int32_t rq = site_at(ed, 2 * d.cx + ex + ox, 2 * d.cy + ey + oy, 2 * d.cz + ez + oz);
+                    if (rp != q) atomicAdd(&D[k][sp[rp]], -1);
+                    if (rq != p) atomicAdd(&D[k][sp[rq]], 1);
+                }
             }
         }
-        double dQ = 0.0;
-        for (int i = 0; i < M; ++i) {
+        __syncthreads();
+        if (valid && lane < ed.S * M) {
+            const int k = lane / M, i = lane - k * M;
+            const int Da = D[k][a], Db = D[k][b], Di = D[k][i];
             double rowsum = 0.0;
             for (int j = 0; j < M; ++j) {
+                const int Dj = D[k][j];
                 int dn = 0;
                 if (a != b) {
-                    if (i == a) dn = j == a ? 2 * D[a] : (j == b ? D[b] - D[a] : D[j]);
-                    else if (i == b) dn = j == b ? -2 * D[b] : (j == a ? D[b] - D[a] : -D[j]);
-                    else if (j == a) dn = D[i];
-                    else if (j == b) dn = -D[i];
+                    if (i == a) dn = j == a ? 2 * Da : (j == b ? Db - Da : Dj);
+                    else if (i == b) dn = j == b ? -2 * Db : (j == a ? Db - Da : -Dj);
+                    else if (j == a) dn = Di;
+                    else if (j == b) dn = -Di;
                 }
-                const int e = (k * M + i) * M + j;
+                const int e = lane * M + j;
                 if (dN_out) dN_out[u * E + e] = dn;
-                const double R = (double)ed.N / (double)(n[i] * n[j] * (int64_t)ed.zk[k]);
-                const double a0 = 1.0 - (double)counts[e] * R;
-                const double d0 = a0 - target[e];
-                const double a1 = 1.0 - (double)(counts[e] + dn) * R;
-                const double d1 = a1 - target[e];
-                rowsum = rowsum + (d1 * d1 - d0 * d0);
+                const double a1 = 1.0 - (double)(cnt[e] + dn) * R[e];
+                const double d1 = a1 - t[e];
+                rowsum = rowsum + (d1 * d1 - old_sq[e]);
             }
-            dQ = dQ + rowsum;
+            row[lane] = rowsum;
         }
-        acc = acc + weight[k] * dQ;
+        __syncthreads();
+        if (here && lane == 0) {
+            double acc = 0.0;
+            for (int k = 0; k < ed.S; ++k) {
+                double dQ = 0.0;
+                for (int i = 0; i < M; ++i) dQ = dQ + row[k * M + i];
+                acc = acc + weight[k] * dQ;
+            }
+            dS_out[u] = valid ? acc : __longlong_as_double(0x7ff8000000000000ll);
+        }
     }
-    dS_out[u] = acc;
 }
 
 __global__ void philox_kernel(const uint32_t *__restrict__ ctr, uint64_t seed, int64_t n,
@@ -466,13 +503,15 @@ hipError_t launch_final_objective(const ChainDesc *descs_dev, int n_chains, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_trial_eval(const EvalDesc &ed, const int8_t *species, const int32_t *counts,
-                             const double *target, const double *weight, int64_t n_pairs,
-                             const int32_t *pairs, double *dS, int32_t *dN, hipStream_t stream) {
-    if (n_pairs <= 0) return hipSuccess;
-    const int blocks = (int)((n_pairs + 127) / 128);
-    hipLaunchKernelGGL(trial_eval_kernel, dim3(blocks), dim3(128), 0, stream, ed, species, counts, target,
-                       weight, n_pairs, pairs, dS, dN);
+hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,
+                             const int32_t *bad, int64_t n_pairs, const int32_t *pairs, double *dS, int32_t *dN,
+                             int32_t *status, hipStream_t stream) {
+    static_assert(kMaxShells * kMaxSpecies == kTrialLanes, "a lane per row of D");
+    const int per = kTrialThreads / kTrialLanes;
+    // at most 8 workgroups per CU, each with many pairs: their tables are made once
+    const int blocks = (int)std::min<int64_t>(std::max<int64_t>(1, (n_pairs + per - 1) / per), 2048);
+    hipLaunchKernelGGL(trial_eval_kernel, dim3(blocks), dim3(kTrialThreads), 0, stream, ed, tw, species, counts, bad,
+                       n_pairs, pairs, dS, dN, status);
     return hipGetLastError();
 }
 
