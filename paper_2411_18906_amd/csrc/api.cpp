@@ -66,48 +66,41 @@ pyhea_status pyhea_sro_eval(const pyhea_lattice *lat, const int8_t *species_dev,
     }
     hipStream_t stream = as_stream(stream_);
     const int E = g.S * g.M * g.M;
-    // device block: counts [E] | bad | alpha [E] | S, F | target [E], weight [S]
-    const size_t o_bad = ((size_t)E * 4 + 7) & ~size_t(7);
-    const size_t o_alpha = o_bad + 8;
-    const size_t o_sf = o_alpha + (size_t)E * 8;
-    const size_t o_tw = o_sf + 16;
+    // device block: bad | counts [E] | sums of the counting
+    const size_t o_part = 256 + (((size_t)E * 4 + 255) & ~size_t(255));
+    const size_t part = count_partial_bytes(g, 1);
     AsyncBuffer buf;
     buf.stream = stream;
-    PYHEA_HIP(pool_alloc(&buf.ptr, o_tw + (size_t)(E + kMaxShells) * 8, stream));
-    char *base = (char *)buf.ptr;
-    int32_t *counts = (int32_t *)base;
-    int32_t *bad = (int32_t *)(base + o_bad);
-    double *tdev = (double *)(base + o_tw);
-    {
-        const pyhea_status s = count_configs(g, 1, species_dev, counts, bad, stream);
-        if (s != PYHEA_OK) return s;
-    }
+    PinnedLease lease;   // (given back after the stream has drained)
+    PYHEA_HIP(pinned_lease(sizeof(OneResult), stream, &lease));
+    PYHEA_HIP(pool_alloc(&buf.ptr, o_part + part, stream));
+    int32_t *bad = (int32_t *)buf.ptr;
+    int32_t *counts = (int32_t *)((char *)buf.ptr + 256);
+    const pyhea_status s = count_configs(g, 1, species_dev, counts, bad, stream, nullptr, nullptr, nullptr,
+                                         part ? (char *)buf.ptr + o_part : nullptr);
+    if (s != PYHEA_OK) return s;
+    SmallTable tw{};
     if (obj) {
-        SmallTable tw{};
         std::memcpy(tw.v, obj->target, E * 8);
         std::memcpy(tw.v + E, obj->weight, g.S * 8);
-        PYHEA_HIP(launch_upload(tw, E + kMaxShells, tdev, stream));
     }
-    // alpha, S and F (Eq. 2-3) on the device, then one read-back
-    EvalDesc ed;
-    fill_eval_desc(g, &ed);
-    PYHEA_HIP(launch_objective_epilogue(ed, 1, counts, bad, obj ? tdev : nullptr, obj ? tdev + E : nullptr,
-                                        (double *)(base + o_sf), (double *)(base + o_alpha), stream));
-    std::vector<char> h(o_tw);
-    PYHEA_HIP(hipMemcpyAsync(h.data(), base, o_tw, hipMemcpyDeviceToHost, stream));
+    OneDesc od{};
+    od.N = (uint32_t)g.N;
+    od.M = g.M;
+    od.S = g.S;
+    for (int k = 0; k < g.S; ++k) od.zk[k] = g.z[k];
+    OneResult *r = (OneResult *)lease.b.p;
+    PYHEA_HIP(launch_objective_one(od, tw, counts, bad, r, stream));
     PYHEA_HIP(hipStreamSynchronize(stream));
-    const int32_t *c32 = (const int32_t *)h.data();
-    int32_t badh;
-    std::memcpy(&badh, h.data() + o_bad, 4);
-    std::vector<int64_t> c64(c32, c32 + E);
-    int64_t n[kMaxSpecies];
-    if (badh || !species_totals(g, c64.data(), n)) {
+    lease.drained = true;
+    if (r->invalid) {
         set_error("species ids must lie in [0, n_species) and every species must occur");
         return PYHEA_EINVAL;
     }
-    if (counts_host) std::memcpy(counts_host, c64.data(), E * 8);
-    if (alpha_host) std::memcpy(alpha_host, h.data() + o_alpha, E * 8);
-    if (obj && S_F_host) std::memcpy(S_F_host, h.data() + o_sf, 16);
+    if (counts_host)
+        for (int e = 0; e < E; ++e) counts_host[e] = r->counts[e];
+    if (alpha_host) std::memcpy(alpha_host, r->alpha, E * 8);
+    if (obj && S_F_host) std::memcpy(S_F_host, r->S_F, 16);
     return guard(PYHEA_OK);
 }
 

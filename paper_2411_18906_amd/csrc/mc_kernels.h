@@ -100,10 +100,25 @@ hipError_t launch_upload(const SmallTable &t, int n, double *dst, hipStream_t st
 
 hipError_t launch_count_gather(const EvalDesc &ed, int64_t K, const int8_t *species,
                                int32_t *counts, int32_t *bad, hipStream_t stream);
-// alpha (optional, [K][S][M][M]) and, with a target, S_F [K][2] from counts.
+// S_F [K][2] from counts.
 hipError_t launch_objective_epilogue(const EvalDesc &ed, int64_t K, const int32_t *counts,
                                      const int32_t *bad, const double *target, const double *weight,
-                                     double *S_F, double *alpha, hipStream_t stream);
+                                     double *S_F, hipStream_t stream);
+// Eq. 2-3 of one configuration into page-locked host memory; a zero table gives the alpha
+// alone (S and F then mean nothing).
+struct OneDesc {
+    uint32_t N;
+    int32_t M, S;
+    int32_t zk[kMaxShells];
+};
+struct OneResult {
+    double S_F[2];
+    double alpha[kMaxShells * kMaxSpecies * kMaxSpecies];
+    int32_t counts[kMaxShells * kMaxSpecies * kMaxSpecies];
+    int32_t invalid;   // an id out of range or a species absent: only this is set
+};
+hipError_t launch_objective_one(const OneDesc &od, const SmallTable &tw, const int32_t *counts, const int32_t *bad,
+                                OneResult *out, hipStream_t stream);
 // `status` is host memory: 1 if an id is invalid or a species absent (nothing else is
 // written then), else 0.
 hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,

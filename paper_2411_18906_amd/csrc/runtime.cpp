@@ -304,7 +304,7 @@ pyhea_status eval_batch(const Geometry &g, int64_t K, const int8_t *species, con
     if (e == hipSuccess && st == PYHEA_OK && obj && !fused) {
         EvalDesc ed;
         fill_eval_desc(g, &ed);
-        e = launch_objective_epilogue(ed, K, counts, bad, tdev, tdev + E, S_F, nullptr, stream);
+        e = launch_objective_epilogue(ed, K, counts, bad, tdev, tdev + E, S_F, stream);
     }
     if (own) (void)hipFreeAsync(own, stream);
     if (e != hipSuccess) return device_error(e, "eval_batch");

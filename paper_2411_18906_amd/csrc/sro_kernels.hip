@@ -170,12 +170,10 @@ __global__ void zero_i32_kernel(int32_t *p, int64_t n) {
 
 // alpha / S / F of Eq. 2-3 per configuration (one thread per configuration),
 // binary64, no contraction: R = N / (n_i n_j z_k), alpha = 1 - N_ij R,
-// Q_k = sum_i (sum_j (alpha - t)^2), S = sum_k w_k Q_k, F = sqrt(S).  alpha
-// [K][S][M][M] is written when non-null, S_F when target is non-null.
+// Q_k = sum_i (sum_j (alpha - t)^2), S = sum_k w_k Q_k, F = sqrt(S).
 __global__ void objective_kernel(EvalDesc ed, int64_t K, const int32_t *__restrict__ counts,
                                  const int32_t *__restrict__ bad, const double *__restrict__ target,
-                                 const double *__restrict__ weight, double *__restrict__ S_F,
-                                 double *__restrict__ alpha) {
+                                 const double *__restrict__ weight, double *__restrict__ S_F) {
     const int64_t kc = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (kc >= K) return;
     const int M = ed.M, E = ed.S * M * M;
@@ -189,10 +187,8 @@ __global__ void objective_kernel(EvalDesc ed, int64_t K, const int32_t *__restri
         ok = ok && n[i] > 0;
     }
     if (!ok) {
-        if (target) {
-            S_F[2 * kc] = __longlong_as_double(0x7ff8000000000000ll);
-            S_F[2 * kc + 1] = __longlong_as_double(0x7ff8000000000000ll);
-        }
+        S_F[2 * kc] = __longlong_as_double(0x7ff8000000000000ll);
+        S_F[2 * kc + 1] = __longlong_as_double(0x7ff8000000000000ll);
         return;
     }
     double sum = 0.0;
@@ -204,20 +200,15 @@ __global__ void objective_kernel(EvalDesc ed, int64_t K, const int32_t *__restri
                 const int e = (k * M + i) * M + j;
                 const double R = (double)ed.N / (double)(n[i] * n[j] * (int64_t)ed.zk[k]);
                 const double a = 1.0 - (double)c[e] * R;
-                if (alpha) alpha[kc * E + e] = a;
-                if (target) {
-                    const double dd = a - target[e];
-                    row = row + dd * dd;
-                }
+                const double dd = a - target[e];
+                row = row + dd * dd;
             }
             Q = Q + row;
         }
-        if (target) sum = sum + weight[k] * Q;
+        sum = sum + weight[k] * Q;
     }
-    if (target) {
-        S_F[2 * kc] = sum;
-        S_F[2 * kc + 1] = sqrt(sum);
-    }
+    S_F[2 * kc] = sum;
+    S_F[2 * kc + 1] = sqrt(sum);
 }
 
 // objective_kernel for a few configurations: one 64-thread block per
@@ -228,7 +219,7 @@ __global__ void __launch_bounds__(64) objective_block_kernel(EvalDesc ed, const 
                                                              const int32_t *__restrict__ bad,
                                                              const double *__restrict__ target,
                                                              const double *__restrict__ weight,
-                                                             double *__restrict__ S_F, double *__restrict__ alpha) {
+                                                             double *__restrict__ S_F) {
     __shared__ int64_t n[kMaxSpecies];
     __shared__ double lsq[kMaxShells * kMaxSpecies * kMaxSpecies];
     __shared__ double lrow[kMaxShells * kMaxSpecies];
@@ -245,7 +236,7 @@ __global__ void __launch_bounds__(64) objective_block_kernel(EvalDesc ed, const 
     bool ok = bad[kc] == 0;
     for (int i = 0; i < M; ++i) ok = ok && n[i] > 0;
     if (!ok) {
-        if (target && tid == 0) {
+        if (tid == 0) {
             S_F[2 * kc] = __longlong_as_double(0x7ff8000000000000ll);
             S_F[2 * kc + 1] = __longlong_as_double(0x7ff8000000000000ll);
         }
@@ -255,13 +246,9 @@ __global__ void __launch_bounds__(64) objective_block_kernel(EvalDesc ed, const 
         const int k = e / (M * M), i = (e / M) % M, j = e % M;
         const double R = (double)ed.N / (double)(n[i] * n[j] * (int64_t)ed.zk[k]);
         const double a = 1.0 - (double)c[e] * R;
-        if (alpha) alpha[kc * E + e] = a;
-        if (target) {
-            const double dd = a - target[e];
-            lsq[e] = dd * dd;
-        }
+        const double dd = a - target[e];
+        lsq[e] = dd * dd;
     }
-    if (!target) return;
     __syncthreads();
     for (int r = tid; r < ed.S * M; r += blockDim.x) {
         double row = 0.0;
@@ -278,6 +265,63 @@ __global__ void __launch_bounds__(64) objective_block_kernel(EvalDesc ed, const 
         }
         S_F[2 * kc] = sum;
         S_F[2 * kc + 1] = sqrt(sum);
+    }
+}
+
+// Eq. 2-3 of a single configuration whose results the host waits for: the target and
+// weights arrive with the arguments and the results go to page-locked host memory, so that
+// nothing is uploaded or read back (a launch, a copy and its staging: 30 us of a call).
+// Expressions and summation order of objective_block_kernel.
+constexpr int kOneThreads = 256;   // S M^2 entries at once
+__global__ void __launch_bounds__(kOneThreads)
+objective_one_kernel(OneDesc od, SmallTable tw, const int32_t *__restrict__ counts, const int32_t *__restrict__ bad,
+                     OneResult *__restrict__ out) {
+    __shared__ int32_t c[kMaxShells * kMaxSpecies * kMaxSpecies];
+    __shared__ int64_t n[kMaxSpecies];
+    __shared__ double lsq[kMaxShells * kMaxSpecies * kMaxSpecies];
+    __shared__ double lrow[kMaxShells * kMaxSpecies];
+    const int tid = (int)threadIdx.x;
+    const int M = od.M, E = od.S * M * M;
+    const int isbad = *bad;
+    if (tid < E) {
+        c[tid] = counts[tid];
+        out->counts[tid] = c[tid];
+    }
+    __syncthreads();
+    if (tid < M) {
+        int64_t r = 0;
+        for (int j = 0; j < M; ++j) r += c[tid * M + j];
+        n[tid] = r / od.zk[0];
+    }
+    __syncthreads();
+    bool ok = isbad == 0;
+    for (int i = 0; i < M; ++i) ok = ok && n[i] > 0;
+    if (tid == 0) out->invalid = ok ? 0 : 1;
+    if (!ok) return;
+    if (tid < E) {
+        const int k = tid / (M * M), i = (tid / M) % M, j = tid % M;
+        const double R = (double)od.N / (double)(n[i] * n[j] * (int64_t)od.zk[k]);
+        const double a = 1.0 - (double)c[tid] * R;
+        out->alpha[tid] = a;
+        const double dd = a - tw.v[tid];
+        lsq[tid] = dd * dd;
+    }
+    __syncthreads();
+    if (tid < od.S * M) {
+        double row = 0.0;
+        for (int j = 0; j < M; ++j) row = row + lsq[tid * M + j];
+        lrow[tid] = row;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double sum = 0.0;
+        for (int k = 0; k < od.S; ++k) {
+            double Q = 0.0;
+            for (int i = 0; i < M; ++i) Q = Q + lrow[k * M + i];
+            sum = sum + tw.v[E + k] * Q;
+        }
+        out->S_F[0] = sum;
+        out->S_F[1] = sqrt(sum);
     }
 }
 
@@ -484,16 +528,23 @@ hipError_t launch_count_tasks(const CountTask *tasks, const uint32_t *tile0, int
 
 hipError_t launch_objective_epilogue(const EvalDesc &ed, int64_t K, const int32_t *counts,
                                      const int32_t *bad, const double *target, const double *weight,
-                                     double *S_F, double *alpha, hipStream_t stream) {
+                                     double *S_F, hipStream_t stream) {
     if (K <= 0) return hipSuccess;
     if (K <= 1024) {   // few configurations: a block each rather than a lane each
         hipLaunchKernelGGL(objective_block_kernel, dim3((unsigned)K), dim3(64), 0, stream, ed, counts, bad, target,
-                           weight, S_F, alpha);
+                           weight, S_F);
         return hipGetLastError();
     }
     const int blocks = (int)((K + 255) / 256);
     hipLaunchKernelGGL(objective_kernel, dim3(blocks), dim3(256), 0, stream, ed, K, counts, bad, target,
-                       weight, S_F, alpha);
+                       weight, S_F);
+    return hipGetLastError();
+}
+
+hipError_t launch_objective_one(const OneDesc &od, const SmallTable &tw, const int32_t *counts, const int32_t *bad,
+                                OneResult *out, hipStream_t stream) {
+    static_assert(kMaxShells * kMaxSpecies * kMaxSpecies <= kOneThreads, "a lane per entry");
+    hipLaunchKernelGGL(objective_one_kernel, dim3(1), dim3(kOneThreads), 0, stream, od, tw, counts, bad, out);
     return hipGetLastError();
 }
 
