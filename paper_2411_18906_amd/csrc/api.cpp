@@ -236,30 +236,31 @@ pyhea_status pyhea_map_sites(const pyhea_lattice *lat, const double *box_host, d
     for (int ax = 0; ax < 3; ++ax) {
         md.L[ax] = g.L[ax];
         md.scale[ax] = 2.0 * g.L[ax] / box_host[ax];
+        md.w[ax] = 1.0 / (md.scale[ax] * md.scale[ax]);
     }
     md.M = g.M;
     md.N = g.N;
     md.max_disp2 = max_disp * max_disp;
-    // device block: flags [4] | owner [N] (unless the caller's)
-    AsyncBuffer buf;
+    AsyncBuffer buf;   // owner [N] (unless the caller's)
     buf.stream = stream;
-    const size_t own = atom_of_site_dev ? 0 : (size_t)g.N * 4;
-    PYHEA_HIP(pool_alloc(&buf.ptr, 256 + own, stream));
-    int32_t *flags = (int32_t *)buf.ptr;
-    int32_t *owner = atom_of_site_dev ? atom_of_site_dev : (int32_t *)((char *)buf.ptr + 256);
-    PYHEA_HIP(launch_map_sites(md, n_atoms, xyz_dev, types_dev, owner, flags, species_dev, stream));
-    int32_t fh[4] = {0, 0, 0, 0};
-    PYHEA_HIP(hipMemcpyAsync(fh, flags, sizeof(fh), hipMemcpyDeviceToHost, stream));
+    PinnedLease lease;   // (given back after the stream has drained)
+    PYHEA_HIP(pinned_lease(64, stream, &lease));
+    volatile int32_t *fh = (volatile int32_t *)lease.b.p;
+    for (int i = 0; i < 3; ++i) fh[i] = 0;
+    if (!atom_of_site_dev) PYHEA_HIP(pool_alloc(&buf.ptr, (size_t)g.N * 4, stream));
+    int32_t *owner = atom_of_site_dev ? atom_of_site_dev : (int32_t *)buf.ptr;
+    PYHEA_HIP(launch_map_sites(md, n_atoms, xyz_dev, types_dev, owner, (int32_t *)lease.b.p, species_dev, stream));
     PYHEA_HIP(hipStreamSynchronize(stream));
+    lease.drained = true;
     if (fh[0]) {
         set_error("an atom lies farther than max_disp from every lattice site");
         return PYHEA_EINVAL;
     }
-    if (fh[2]) {
+    if (fh[1]) {
         set_error("atom types must lie in [0, n_species)");
         return PYHEA_EINVAL;
     }
-    if (fh[1] || fh[3]) {
+    if (fh[2]) {
         set_error("two atoms are nearest to one lattice site (another site is vacant)");
         return PYHEA_EINVAL;
     }

@@ -13,12 +13,13 @@ struct SiteMapDesc {
     int32_t M;           // species ids must lie in [0, M)
     int64_t N;           // sites
     double scale[3];     // half lattice units per unit of length, per axis (2 L / box)
+    double w[3];         // squared length of a half unit, 1 / scale^2
     double max_disp2;    // squared largest accepted displacement (length units)
 };
 
-// owner [N] int32 and flags [4] int32 are device scratch (the entry point's or
-// the caller's): flags = {displacement too large, two atoms on one site, type
-// out of range, vacant site}.  Writes species [N].
+// owner [N] int32 is device scratch (the entry point's or the caller's); flags [3]
+// int32 is host memory, zero before the launch: {displacement too large, type out of
+// range, vacant site}.  Writes species [N].
 hipError_t launch_map_sites(const SiteMapDesc &md, int64_t n, const double *xyz, const int8_t *types,
                             int32_t *owner, int32_t *flags, int8_t *species, hipStream_t stream);
 
