@@ -559,9 +559,8 @@ pyhea_status pyhea_global_search(const pyhea_lattice *lat, const pyhea_objective
                          [&](int a, int b) { return sf[2 * a + 1] < sf[2 * b + 1]; });
         // local search of the n_refine best, in rank order
         std::vector<ChainJob> jobs(T, proto);
+        PYHEA_HIP(launch_copy_rows(order.data(), T, N, pool, refine, stream));
         for (int r = 0; r < T; ++r) {
-            PYHEA_HIP(hipMemcpyAsync(refine + (int64_t)r * N, pool + (int64_t)order[r] * N, N,
-                                     hipMemcpyDeviceToDevice, stream));
             jobs[r].species_dev = refine + (int64_t)r * N;
             jobs[r].params.chain_id = (uint32_t)(t * n + order[r]);
         }
@@ -581,9 +580,7 @@ pyhea_status pyhea_global_search(const pyhea_lattice *lat, const pyhea_objective
         }
         if (history_host) history_host[t] = st.F;
         // the best R refined solutions seed the next iteration
-        for (int i = 0; i < R; ++i)
-            PYHEA_HIP(hipMemcpyAsync(pool + (int64_t)i * N, refine + (int64_t)rank[i] * N, N,
-                                     hipMemcpyDeviceToDevice, stream));
+        PYHEA_HIP(launch_copy_rows(rank.data(), R, N, refine, pool, stream));
         kept = R;
     }
     PYHEA_HIP(hipStreamSynchronize(stream));

@@ -119,6 +119,12 @@ struct OneResult {
 };
 hipError_t launch_objective_one(const OneDesc &od, const SmallTable &tw, const int32_t *counts, const int32_t *bad,
                                 OneResult *out, hipStream_t stream);
+// Row r of dst [count][N] becomes row rows[r] of src (N < 2^32; no overlap).
+constexpr int kCopyRows = 256;
+struct RowTable {
+    int32_t row[kCopyRows];
+};
+hipError_t launch_copy_rows(const int *rows, int count, int64_t N, const int8_t *src, int8_t *dst, hipStream_t stream);
 // `status` is host memory: 1 if an id is invalid or a species absent (nothing else is
 // written then), else 0.
 hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,

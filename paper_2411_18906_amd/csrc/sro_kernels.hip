@@ -487,6 +487,17 @@ __global__ void philox_kernel(const uint32_t *__restrict__ ctr, uint64_t seed, i
     for (int w = 0; w < 4; ++w) out[4 * i + w] = c[w];
 }
 
+// Row r of dst is row t.row[r] of src, N bytes each; T divides N and the bases.  One
+// launch for up to kCopyRows rows: bound by the launch, where a copy command per row kept
+// the device waiting for the next (a search of 6 iterations with 48 rows of 32,000 bytes
+// each: 35.0 -> 32.8 ms).
+template <class T>
+__global__ void copy_rows_kernel(RowTable t, uint32_t n, const T *__restrict__ src, T *__restrict__ dst) {
+    const T *s = src + (int64_t)t.row[blockIdx.y] * n;
+    T *d = dst + (int64_t)blockIdx.y * n;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) d[i] = s[i];
+}
+
 }  // namespace
 
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t stream) {
@@ -552,6 +563,29 @@ hipError_t launch_final_objective(const ChainDesc *descs_dev, int n_chains, hipS
     if (n_chains <= 0) return hipSuccess;
     hipLaunchKernelGGL(final_objective_kernel, dim3((n_chains + 63) / 64), dim3(64), 0, stream, descs_dev, n_chains);
     return hipGetLastError();
+}
+
+hipError_t launch_copy_rows(const int *rows, int count, int64_t N, const int8_t *src, int8_t *dst,
+                            hipStream_t stream) {
+    const uintptr_t all = (uintptr_t)src | (uintptr_t)dst | (uintptr_t)N;
+    for (int r0 = 0; r0 < count; r0 += kCopyRows) {
+        RowTable t{};
+        const int n = std::min(count - r0, kCopyRows);
+        for (int r = 0; r < n; ++r) t.row[r] = rows[r0 + r];
+        int8_t *d = dst + (int64_t)r0 * N;
+        const auto grid = [&](int64_t items) { return dim3((unsigned)std::min<int64_t>((items + 255) / 256, 256), n); };
+        if (all % 16 == 0)
+            hipLaunchKernelGGL(copy_rows_kernel<int4>, grid(N / 16), dim3(256), 0, stream, t, (uint32_t)(N / 16),
+                               (const int4 *)src, (int4 *)d);
+        else if (all % 4 == 0)
+            hipLaunchKernelGGL(copy_rows_kernel<int32_t>, grid(N / 4), dim3(256), 0, stream, t, (uint32_t)(N / 4),
+                               (const int32_t *)src, (int32_t *)d);
+        else
+            hipLaunchKernelGGL(copy_rows_kernel<int8_t>, grid(N), dim3(256), 0, stream, t, (uint32_t)N, src, d);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,
