@@ -220,8 +220,8 @@ def recorded_traffic():
     rocprofv3 counter summary, if that summary was taken on the current kernel
     source (otherwise None)."""
     import hashlib
-    prof = os.path.join(ROOT, "profiles", "full_eval_fcc20_5sp_traffic.md")
-    src = os.path.join(ROOT, "paper_2411_18906_amd", "csrc", "sro_bits.hip")
+    prof = os.path.join(ROOT, "profiles", "full_eval_matrix_cores.md")
+    src = os.path.join(ROOT, "paper_2411_18906_amd", "csrc", "sro_mfma.hip")
     try:
         text = open(prof).read()
         sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
@@ -564,7 +564,7 @@ def main():
                            "traffic": None if tb is None else tb / (ms.mean() / 1e3) / 1e9,
                            "kernel": "full SRO evaluation (pair counts + objective) of the batch"}
         # the same kernel against the VALU issue rate, from its recorded instruction count
-        ops = recorded("full_eval_fcc20_5sp_traffic.md", "sro_bits.hip", "valu_lane_ops_per_site")
+        ops = recorded("full_eval_matrix_cores.md", "sro_mfma.hip", "valu_lane_ops_per_site")
         if ops is not None:
             cap = VALU_LANE_OPS_PEAK / ops / 1e9   # GB/s at one byte per site
             out["roofline_valu"] = {"bound": "alu", "lane_ops_per_site": ops, "valu_cap_GBps": cap,

@@ -105,7 +105,8 @@ typedef struct {
     double F;            /* sqrt(S), Eq. 3                                      */
     int64_t log_len;     /* accepted-swap records written (min(commits, cap))  */
     int32_t shape;       /* launch shape used: store (0 LDS bytes, 1 LDS nibbles,
-                            2 HBM) * 10000 + steps per pass * 100 + commit chunk */
+                            2 HBM) * 10000 + (1 if quiet steps go one by one, else more)
+                            * 100 + commit chunk */
     int32_t shape_measured; /* 1 if that shape was chosen by measurement (this
                             call or an earlier one), 0 by the cost model      */
     int32_t graph;       /* 1 if the call's device work ran as a replay of the
@@ -379,14 +380,13 @@ pyhea_status pyhea_philox4x32_10(const uint32_t *ctr_dev, uint64_t seed, int64_t
                                  uint32_t *out_dev, void *stream);
 
 /* Launch shape of the MC kernels.  The library picks it from the chain's
- * size and the number of chains launched together: of the stores (LDS bytes,
- * LDS nibbles, HBM), steps per pass and speculative commit chunks that fit the
- * LDS, the combination with the best measured rate, one wavefront per shell,
- * and a block small enough that every chain of the call can be resident.
- * This switch forces one shape family process-wide: -1 = automatic, 0 =
- * automatic, 1 = LDS nibbles or HBM, 2 = HBM, 3 = automatic, 4 = offsets
- * spread evenly over the shell wavefronts, 5 = DISJOINT commits decided one by
- * one, 6 = speculative commit chunks of 4 candidates.  Shapes never change
+ * size and the number of chains launched together: the first of the stores LDS
+ * bytes, LDS nibbles and HBM in which the chain fits, a block small enough that
+ * every chain of the call can be resident, quiet steps in windows, and commit
+ * chunks of the size that fits the LDS.
+ * This switch forces one shape family process-wide: -1, 0, 3, 4 = automatic,
+ * 1 = LDS nibbles or HBM, 2 = HBM, 5 = DISJOINT commits decided one by
+ * one, 6 = commit chunks of 4 candidates.  Shapes never change
  * results; EINVAL outside -1..6. */
 pyhea_status pyhea_tune_force(int32_t variant);
 
@@ -394,9 +394,8 @@ pyhea_status pyhea_tune_force(int32_t variant);
  * (pyhea_mc_run; on by default): the first chain of a kind -- device, lattice,
  * M, S, B, floor(log2 padded sites) -- is counted on a scratch copy, run past
  * its first steps, and from that saved state run again under each candidate
- * shape (per store that fits: the most steps per pass the wave budget allows,
- * about half of that and one, each with the largest commit chunk that fits
- * and with commits one by one, and the cost model's own shape) for two
+ * shape (per store that fits: quiet steps in windows and step by step, with
+ * the largest commit chunk that fits, and the cost model's own shape) for two
  * lengths, whose time difference (median of three) is the per-step cost; the
  * cost model's shape is kept unless another is at least 3 % cheaper per step,
  * and the choice is kept in memory and in the text file
@@ -437,13 +436,11 @@ pyhea_status pyhea_tune_force_eval(int32_t kernel);
  * Process-wide; shapes never change results; EINVAL outside those values. */
 pyhea_status pyhea_tune_force_stream(int32_t layers_per_group, int32_t threads);
 
-/* Steps whose candidates one pass of the MC kernel evaluates at once: 0 =
- * automatic (the largest value up to 8 whose block still lets every chain of
- * the call, or every slot of a server, be resident on the GPU at once), or
- * 1..8 (capped so that a block has at most 16 wavefronts).  Candidates are
- * drawn from counters, not from the state, so the candidates of later steps
- * can be evaluated against the current state; a
- * step's evaluation is used only if every earlier step of the pass committed
+/* Whether the MC kernel evaluates the steps after one without a commit in
+ * windows, a slot group per wavefront: 0 = automatic (yes), 1 = step by step,
+ * 2..8 = windows.  Candidates are drawn from counters, not from the state, so
+ * the candidates of later steps can be evaluated against the current state; a
+ * step's evaluation is used only if every earlier step of the window committed
  * nothing (the state is then unchanged).  Trajectories are bit-identical for
  * every value.  Process-wide; EINVAL outside 0..8. */
 pyhea_status pyhea_tune_force_lookahead(int32_t steps);

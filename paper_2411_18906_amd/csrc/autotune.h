@@ -70,7 +70,7 @@ void set_forced_eval_kernel(int v);
 // Streaming evaluation shape forced through pyhea_tune_force_stream (0 = automatic).
 void forced_stream_shape(int *layers_per_group, int *threads);
 void set_forced_stream_shape(int layers_per_group, int threads);
-// Steps per pass forced through pyhea_tune_force_lookahead (0 = automatic).
+// Windows of quiet steps forced through pyhea_tune_force_lookahead (0 = automatic, 1 = none).
 int forced_lookahead();
 void set_forced_lookahead(int k);
 
