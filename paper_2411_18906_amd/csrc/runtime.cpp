@@ -204,13 +204,18 @@ bool mfma_shape(const Geometry &g, int64_t K, MfmaDesc *md) {
 }
 }  // namespace
 
-size_t count_partial_bytes(const Geometry &g, int64_t K) {
+namespace {
+size_t bit_partial_bytes(const Geometry &g, int64_t K) {
     BitDesc bd;
     StreamDesc sd;
-    MfmaDesc md;
-    if (K > 0 && mfma_shape(g, K, &md)) return mfma_partial_bytes(md, K);
     if (K <= 0 || stream_shape(g, K, &sd) || !bit_shape(g, K, &bd) || bd.nchunks <= 1) return 0;
     return (size_t)K * bd.nchunks * bd.partial_stride * 4;
+}
+}  // namespace
+
+size_t count_partial_bytes(const Geometry &g, int64_t K) {
+    MfmaDesc md;
+    return K > 0 && mfma_shape(g, K, &md) ? mfma_partial_bytes(md, K) : bit_partial_bytes(g, K);
 }
 
 pyhea_status count_configs(const Geometry &g, int64_t K, const int8_t *species, int32_t *counts,
@@ -274,7 +279,12 @@ EvalScratch eval_scratch_layout(const Geometry &g, int64_t K) {
 }
 }  // namespace
 
-size_t eval_batch_scratch_bytes(const Geometry &g, int64_t K) { return eval_scratch_layout(g, K).total; }
+// The larger of the kernels' needs: whether a batch fits a given scratch does not change
+// with the kernel that counts it.
+size_t eval_batch_scratch_bytes(const Geometry &g, int64_t K) {
+    const EvalScratch l = eval_scratch_layout(g, K);
+    return std::max(l.total, l.partial + bit_partial_bytes(g, K));
+}
 
 pyhea_status eval_batch(const Geometry &g, int64_t K, const int8_t *species, const pyhea_objective *obj,
                         int32_t *counts, double *S_F, hipStream_t stream, void *scratch) {

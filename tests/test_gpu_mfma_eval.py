@@ -107,3 +107,27 @@ def test_nearly_one_species(lattice, L, S, K, most):
     c = counts.cpu().numpy()
     for k in (0, K - 1):
         np.testing.assert_array_equal(c[k], want)
+
+
+def test_fixed_scratch_limit_is_the_same_for_every_kernel():
+    """A batch is refused by the fixed scratch for the same numbers of configurations
+    whichever kernel counts it."""
+    lattice, L, M, S = orc.FCC, (40, 40, 40), 4, 2
+    N = orc.n_sites(lattice, L)
+
+    def refused(K, kernel):
+        pb.pyhea_tune_force_eval(kernel)
+        try:
+            pb.pyhea_sro_eval_batch_noalloc(lattice, L, M, S, species[:K], counts[:K])
+            torch.cuda.synchronize()
+            return False
+        except pb.PyheaError:
+            return True
+        finally:
+            pb.pyhea_tune_force_eval(-1)
+
+    most = 130000         # flags and two bit-sliced workgroups' 64 bytes each: 17.2 MB > the 16 MiB array
+    species = torch.zeros((most, N), dtype=torch.int8, device="cuda")
+    counts = torch.zeros((most, S, M, M), dtype=torch.int32, device="cuda")
+    got = [(refused(K, -1), refused(K, 1)) for K in (100, 4096, most)]
+    assert all(a == b for a, b in got) and not got[0][0] and not got[1][0] and got[2][0]
