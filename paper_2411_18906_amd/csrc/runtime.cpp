@@ -672,12 +672,13 @@ hipError_t record_plan(ChainPlan *p, Work &work) {
 }
 
 // Calls that scan (run_chains): chains at most, steps of the longest at least.
-// Below kWideSteps the launches cost more than the scan saves (FCC 4^3, 157
-// steps: 337 us per call without, 333 us with it); many chains keep the CUs busy
-// by themselves, and the windows of more chains than kWideChains would wait for
-// the slowest chain of each round.
+// Below kWideSteps the rounds' launches cost more than the scan saves (us per call
+// without / with: 130 steps FCC 4^3 260 / 273, FCC 8^3 436 / 467, BCC 16^3 393 / 417; 200
+// steps 303 / 310, 499 / 552, 447 / 472, FCC 20^3 801 / 793; 300 steps 345 / 295, 572 / 650,
+// 492 / 467, 920 / 904); many chains keep the CUs busy by themselves, and the windows of
+// more chains than kWideChains would wait for the slowest chain of each round.
 constexpr int kWideChains = 16;
-constexpr int kWideSteps = 128;
+constexpr int kWideSteps = 224;
 // Steps without a commit after which a chain goes to the scan: a round (two
 // launches, the LDS fills, one evaluation) costs about as much as these steps on
 // one CU.
