@@ -729,7 +729,8 @@ bool fill_mfma_desc(const Geometry &g, int lds_budget, int64_t K, MfmaDesc *md) 
     const int most = (int)std::max<int64_t>(1, (Ly + want - 1) / want);
     double best = 0;
     int last_n = 0;
-    for (int ys0 = most; ys0 >= 1; --ys0) {
+    const int fit = (int)std::min<int64_t>(most, (lds_budget / 2 - fixed) / per_row);   // (two workgroups on a CU)
+    for (int ys0 = fit; ys0 >= 1; --ys0) {
         const int n = (Ly + ys0 - 1) / ys0;
         if (n == last_n) continue;
         last_n = n;
