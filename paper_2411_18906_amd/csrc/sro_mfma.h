@@ -9,6 +9,25 @@ namespace pyhea {
 
 constexpr int kMfmaTiles = 14;     // (column, layer) displacements of a launch at most
 constexpr int kMfmaGroups = kMaxShells + 1;   // sums per configuration: the shells, and each site with itself
+// cells a workgroup may count: a displacement's sums of 16 * 4 quarter units per cell stay below 2^24
+// (and kQuarter + sum at most 2^22)
+constexpr int kMfmaMaxCells = 1 << 16;
+
+// Feature sums are whole numbers of quarters: a pair that counts 1 weighs up to 64.  A
+// workgroup's (at most 4 sublattices x 12 neighbours x kMfmaMaxCells pairs, 2^27.6) fit 32
+// bits.  A configuration's, up to 32 N z, do not where N z >= 2^26, and since they are
+// divided on the way to counts they must not wrap: 64 bits.
+typedef int32_t MfmaGroupSum;
+typedef int64_t MfmaSum;
+
+// a_i of species i < 4 from four feature sums doubled (f' = 2 f)
+template <class Sum>
+__host__ __device__ inline void species_of_features(Sum f0, Sum f1, Sum f2, Sum f3, Sum *a) {
+    a[3] = (f3 - f1 - f2) / 2;
+    a[0] = f0;
+    a[1] = f1 / 2 - a[3];
+    a[2] = f2 / 4 - a[3];
+}
 
 struct MfmaDesc {
     int32_t Lx, Ly, Lz, M, S;

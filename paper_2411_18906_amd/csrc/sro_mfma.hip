@@ -9,7 +9,7 @@
 // determine the pair counts.  A matrix instruction of 16 rows (sublattice and
 // feature at a cell), 16 columns (sublattice and feature at the displaced cell)
 // and 128 cells adds the products of one displacement: products are at most 16 and
-// multiples of 1/4, and a wavefront counts at most kMaxCells cells, so every
+// multiples of 1/4, and a wavefront counts at most kMfmaMaxCells cells, so every
 // binary32 sum is exact.
 //
 // Layout: word q of a column (x, y) and a sublattice holds layers W p + q - dead in its
@@ -60,9 +60,6 @@ using v4i = int __attribute__((ext_vector_type(4)));
 using v8i = int __attribute__((ext_vector_type(8)));
 using v4f = float __attribute__((ext_vector_type(4)));
 
-// cells a workgroup may count: a displacement's sums of 16 * 4 quarter units per cell stay below 2^24
-// (and kQuarter + sum below 2^22)
-constexpr int kMaxCells = 1 << 16;
 // a float whose last bit is 1/4: its bits count the quarters added to it.  Integers because
 // the LDS adds floats at a lane per 3 cycles (five times the whole kernel's time).
 constexpr float kQuarter = 1.5f * (1 << 21);
@@ -78,18 +75,11 @@ __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel)
     return __builtin_amdgcn_perm(hi, lo, sel);
 }
 
-// a_i of species i < 4 from four feature sums doubled (f' = 2 f)
-__device__ __forceinline__ void species_of_features(int f0, int f1, int f2, int f3, int *a) {
-    a[3] = (f3 - f1 - f2) / 2;
-    a[0] = f0;
-    a[1] = f1 / 2 - a[3];
-    a[2] = f2 / 4 - a[3];
-}
-
 // Counts and Eq. 2-3 of one configuration from its feature sums F [groups][4][4]
 // (units of 1/4; group S: sites with themselves) and the invalid-id flag.
+template <class Sum>
 struct FinishLds {
-    int32_t G[kMfmaGroups][16];
+    Sum G[kMfmaGroups][16];
     int32_t n[8];
     int32_t lc[kMaxShells * 25];
     double lsq[kMaxShells * 25];
@@ -97,23 +87,24 @@ struct FinishLds {
 };
 constexpr int kFinishThreads = 128;   // S M^2 <= 100 entries at once: 6,500 clocks, 11,000 by one wavefront
 // The workgroup's first two wavefronts (all that are left of it) call it.
-__device__ __forceinline__ void finish(const int32_t *F, bool bad, const MfmaDesc &md, FinishLds &l, int32_t *cnt,
+template <class Sum>
+__device__ __forceinline__ void finish(const Sum *F, bool bad, const MfmaDesc &md, FinishLds<Sum> &l, int32_t *cnt,
                                        int32_t *bad_out, const double *tw, double *S_F) {
     const int M = md.M, S = md.S, P = M - 1;
     const int tid = (int)threadIdx.x;
     const int g = tid >> 2, u = tid & 3;
     // rows of features to species, then columns: the sums by species pairs
     if (g <= S) {
-        int a[4];
+        Sum a[4];
         species_of_features(F[g * 16 + u], F[g * 16 + 4 + u], F[g * 16 + 8 + u], F[g * 16 + 12 + u], a);
         for (int i = 0; i < 4; ++i) l.G[g][4 * i + u] = a[i];
     }
     __syncthreads();
     if (g <= S) {
-        int a[4];
+        Sum a[4];
         species_of_features(l.G[g][4 * u], l.G[g][4 * u + 1], l.G[g][4 * u + 2], l.G[g][4 * u + 3], a);
         for (int j = 0; j < 4; ++j) l.G[g][4 * u + j] = a[j];
-        if (g == S) l.n[u] = u == 0 ? a[0] : u == 1 ? a[1] : u == 2 ? a[2] : a[3];
+        if (g == S) l.n[u] = (int32_t)(u == 0 ? a[0] : u == 1 ? a[1] : u == 2 ? a[2] : a[3]);
     }
     __syncthreads();
     const int32_t n_last = (int32_t)md.N - l.n[0] - l.n[1] - l.n[2] - l.n[3];   // (species beyond P are 0)
@@ -123,7 +114,7 @@ __device__ __forceinline__ void finish(const int32_t *F, bool bad, const MfmaDes
         int32_t r = md.zk[g] * l.n[u];   // (modulo 2^32; the counts themselves fit)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int32_t v = l.G[g][4 * u + j] + l.G[g][4 * j + u];
+            const int32_t v = (int32_t)(l.G[g][4 * u + j] + l.G[g][4 * j + u]);
             r -= v;   // (0 beyond P)
             if (u < P && j < P) c[u * M + j] = v;
         }
@@ -177,10 +168,10 @@ __device__ __forceinline__ void finish(const int32_t *F, bool bad, const MfmaDes
 }
 
 struct Shared {
-    int32_t F[kMfmaGroups * 16];
+    MfmaGroupSum F[kMfmaGroups * 16];
     int32_t bad;
     uint8_t list[kMfmaTiles * 16];
-    FinishLds fin;
+    FinishLds<MfmaGroupSum> fin;
 };
 constexpr int kFixedLds = (int)((sizeof(Shared) + 15) & ~size_t(15));
 
@@ -521,12 +512,12 @@ count_mfma_kernel(MfmaDesc md, int64_t K, const int8_t *__restrict__ species, in
 __global__ void __launch_bounds__(kFinishThreads) finalize_mfma_kernel(MfmaDesc md, const int32_t *__restrict__ partial,
                                                            int32_t *__restrict__ counts, int32_t *__restrict__ bad,
                                                            const double *__restrict__ tw, double *__restrict__ S_F) {
-    __shared__ int32_t F[kMfmaGroups * 16 + 1];
-    __shared__ FinishLds fin;
+    __shared__ MfmaSum F[kMfmaGroups * 16 + 1];
+    __shared__ FinishLds<MfmaSum> fin;
     const int64_t kc = blockIdx.x;
     const int32_t *p = partial + kc * md.nchunks * (int64_t)kMfmaPartial;
     for (int i = threadIdx.x; i < kMfmaGroups * 16 + 1; i += blockDim.x) {
-        int32_t v = 0;
+        MfmaSum v = 0;
         for (int c = 0; c < md.nchunks; ++c) v += p[c * kMfmaPartial + i];   // the flags add up to > 0
         F[i] = v;
     }
@@ -774,7 +765,7 @@ bool fill_mfma_desc(const Geometry &g, int lds_budget, int64_t K, MfmaDesc *md) 
         const int64_t bytes = K > (1 << 20) ? int64_t(1) << 20 : int64_t(8) << 20;
         md->step = (int32_t)std::max<int64_t>(8, bytes / (md->nchunks * kMfmaPartial * 4) / 8 * 8);
     }
-    return (int64_t)md->ys * g.L[0] * g.L[2] <= kMaxCells;
+    return (int64_t)md->ys * g.L[0] * g.L[2] <= kMfmaMaxCells;
 }
 
 size_t mfma_partial_bytes(const MfmaDesc &md, int64_t K) {

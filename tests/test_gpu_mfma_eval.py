@@ -131,3 +131,25 @@ def test_fixed_scratch_limit_is_the_same_for_every_kernel():
     counts = torch.zeros((most, S, M, M), dtype=torch.int32, device="cuda")
     got = [(refused(K, -1), refused(K, 1)) for K in (100, 4096, most)]
     assert all(a == b for a, b in got) and not got[0][0] and not got[1][0] and got[2][0]
+
+
+@pytest.mark.parametrize("lattice,L,M,S", [(orc.FCC, (120, 120, 120), 5, 3), (orc.FCC, (120, 120, 120), 4, 3),
+                                           (orc.FCC, (60, 511, 60), 5, 4), (orc.BCC, (190, 190, 190), 5, 3)])
+@pytest.mark.parametrize("fractions", [(0.01, 0.01, 0.01, 0.96, 0.01), (0.05, 0.05, 0.05, 0.8, 0.05)])
+def test_large_cells(lattice, L, M, S, fractions):
+    """N z beyond 2^27: 64 quarter units a pair are more than 32 bits hold."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    p = torch.tensor(fractions[5 - M:], device="cuda")
+    edges = torch.cumsum(p / p.sum(), 0)[:-1]
+    u = torch.rand(orc.n_sites(lattice, L), device="cuda", generator=g)
+    sp = torch.bucketize(u, edges).to(torch.int8).unsqueeze(0)
+    got = torch.zeros((2, S, M, M), dtype=torch.int32, device="cuda")
+    pb.pyhea_sro_eval_batch(lattice, L, M, S, sp, got[:1])
+    pb.pyhea_tune_force_eval(0)
+    try:
+        pb.pyhea_sro_eval_batch(lattice, L, M, S, sp, got[1:])
+    finally:
+        pb.pyhea_tune_force_eval(-1)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])
