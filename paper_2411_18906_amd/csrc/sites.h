@@ -17,6 +17,15 @@ struct SiteMapDesc {
     double max_disp2;    // squared largest accepted displacement (length units)
 };
 
+// r modulo m, in [0, m).  Positions reduced into the box decode to -1 .. m + 1, so the
+// division is rare; but beyond about 2^53 periods the reduction in binary64 leaves any
+// residual, and the site must still be one of the box's.
+__host__ __device__ inline int wrap_site(int r, int m) {
+    if ((unsigned)r < (unsigned)m) return r;
+    r %= m;
+    return r < 0 ? r + m : r;
+}
+
 // owner [N] int32 is device scratch (the entry point's or the caller's); flags [3]
 // int32 is host memory, zero before the launch: {displacement too large, type out of
 // range, vacant site}.  Writes species [N].

@@ -100,8 +100,7 @@ __global__ void map_atoms_kernel(SiteMapDesc md, int64_t n, const double *__rest
     if (unknown) return;
     int c[3], par[3];
     for (int ax = 0; ax < 3; ++ax) {
-        const int m = 2 * md.L[ax];
-        const int v = r[ax] < 0 ? r[ax] + m : r[ax] >= m ? r[ax] - m : r[ax];   // from -1 .. m + 1
+        const int v = wrap_site(r[ax], 2 * md.L[ax]);
         c[ax] = v >> 1;
         par[ax] = v & 1;
     }

@@ -1,6 +1,7 @@
 // Host side of the library, called by test_host_checks.py: the arithmetic and the launch
 // shapes that kernels share with the host.
 #include "geometry.h"
+#include "sites.h"
 #include "sro_mfma.h"
 
 using namespace pyhea;
@@ -27,4 +28,8 @@ extern "C" void feature_round_trip(const int64_t *H, int64_t *out) {
         species_of_features(G[4 * i], G[4 * i + 1], G[4 * i + 2], G[4 * i + 3], a);
         for (int j = 0; j < 4; ++j) out[4 * i + j] = a[j];
     }
+}
+
+extern "C" void wrap_sites(const int32_t *r, int64_t n, int32_t m, int32_t *out) {
+    for (int64_t i = 0; i < n; ++i) out[i] = wrap_site(r[i], m);
 }

@@ -23,3 +23,13 @@ def test_pair_sums_of_large_cells(species, total):
     host_checks.lib().feature_round_trip(_p(H), _p(out))
     np.testing.assert_array_equal(out, H)
 
+
+
+@pytest.mark.parametrize("m", [2, 6, 20, 80, 1022])
+def test_decoded_sites_stay_in_the_box(m):
+    """Whatever a position decodes to is a coordinate of the box, its residue modulo m."""
+    r = np.concatenate([np.arange(-3 * m - 3, 3 * m + 4), [-2**31, -2**31 + 1, 2**31 - 1, -4096, 4096, -128, 64],
+                        np.random.default_rng(m).integers(-2**31, 2**31, 1000)]).astype(np.int32)
+    out = np.empty_like(r)
+    host_checks.lib().wrap_sites(_p(r), ctypes.c_int64(len(r)), m, _p(out))
+    np.testing.assert_array_equal(out, r.astype(np.int64) % m)
