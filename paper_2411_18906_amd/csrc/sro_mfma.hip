@@ -301,6 +301,7 @@ count_mfma_kernel(MfmaDesc md, int64_t K, const int8_t *__restrict__ species, in
     for (int i = tid; i < kT * 4; i += nthreads)
         reinterpret_cast<uint32_t *>(sh.list)[i] = reinterpret_cast<const uint32_t *>(md.list)[i];
 
+    bool bad = false;
     // ---- 1. codes: a lane makes the fragments of an (x, row, q), all sublattices ----------
     {
         const uint8_t *cfg = reinterpret_cast<const uint8_t *>(species) + kc * (int64_t)md.N;
@@ -406,10 +407,10 @@ count_mfma_kernel(MfmaDesc md, int64_t K, const int8_t *__restrict__ species, in
                 }
             }
         }
-        // (read by the others after the barrier)
-        if ((bad_id & 0xF8F8F8F8u) != 0 || (bad_code & 0x88888888u) != 0) sh.bad = 1;
+        bad = (bad_id & 0xF8F8F8F8u) != 0 || (bad_code & 0x88888888u) != 0;
     }
     __syncthreads();
+    if (bad) sh.bad = 1;   // after the barrier: thread 0 has cleared it by then (read after further ones)
     if constexpr (!kQ) {   // the columns beside the quarters
         const uint32_t *Dw = reinterpret_cast<const uint32_t *>(D);
         for (int i = tid; i < R * W * A * 2; i += nthreads) {

@@ -153,3 +153,21 @@ def test_large_cells(lattice, L, M, S, fractions):
         pb.pyhea_tune_force_eval(-1)
     torch.cuda.synchronize()
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("lattice,L,step", [(orc.FCC, (9, 8, 7), 1), (orc.FCC, (20, 20, 20), 53), (orc.BCC, (9, 8, 7), 1),
+                                            (orc.FCC, (40, 40, 40), 997), (orc.BCC, (31, 31, 31), 211)])
+def test_an_invalid_id_anywhere(lattice, L, step):
+    """One invalid id, at every site in turn (whichever wavefront reads it): that
+    configuration alone is NaN."""
+    N, M, S = orc.n_sites(lattice, L), 5, 3
+    sites = torch.arange(0, N, step, device="cuda")
+    K = len(sites) + 1
+    sp = torch.from_numpy(wl.iid_configs(N, M, 1, seed=5)).cuda().repeat(K, 1)
+    sp[torch.arange(K - 1, device="cuda"), sites] = torch.tensor([5, 7, 8, -1, 127], dtype=torch.int8, device="cuda")[sites % 5]
+    counts = torch.zeros((K, S, M, M), dtype=torch.int32, device="cuda")
+    SF = torch.zeros((K, 2), dtype=torch.float64, device="cuda")
+    pb.pyhea_sro_eval_batch(lattice, L, M, S, sp, counts, np.zeros((S, M, M)), np.ones(S), SF)
+    torch.cuda.synchronize()
+    nan = torch.isnan(SF).all(dim=1)
+    assert nan[:-1].all() and not nan[-1]
