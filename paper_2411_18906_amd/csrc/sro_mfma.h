@@ -55,6 +55,12 @@ struct MfmaDesc {
 // Fills md; false if the matrix-core kernel does not cover the geometry (it covers 2 to 5
 // species, FCC shells 1-4 and BCC shells 1-3) or is not the faster one there.
 bool fill_mfma_desc(const Geometry &g, int lds_budget, int64_t K, MfmaDesc *md);
+// Configurations one launch takes: a grid holds less than 2^32 threads, and a
+// configuration's workgroups lie eight blocks apart.
+constexpr int64_t mfma_configs_per_launch(int threads, int nchunks) {
+    return ((int64_t(1) << 32) - 1) / threads / nchunks / 8 * 8;
+}
+
 // int32 of scratch per workgroup of a configuration that spans several
 constexpr int kMfmaPartial = kMfmaGroups * 16 + 4;
 

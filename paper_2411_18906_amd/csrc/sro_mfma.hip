@@ -761,7 +761,7 @@ bool fill_mfma_desc(const Geometry &g, int lds_budget, int64_t K, MfmaDesc *md) 
     md->inv_R = 1.0 / md->R;
     md->even = g.L[0] % 4 == 0 && Ly % 4 == 0 && md->ys % 4 == 0;
     // configurations per launch: their sums share the scratch
-    md->step = (1 << 30) / md->nchunks / 8 * 8;
+    md->step = (int32_t)mfma_configs_per_launch(md->threads, md->nchunks);
     if (md->nchunks > 1) {
         const int64_t bytes = K > (1 << 20) ? int64_t(1) << 20 : int64_t(8) << 20;
         md->step = (int32_t)std::max<int64_t>(8, bytes / (md->nchunks * kMfmaPartial * 4) / 8 * 8);

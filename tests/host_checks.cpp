@@ -33,3 +33,21 @@ extern "C" void feature_round_trip(const int64_t *H, int64_t *out) {
 extern "C" void wrap_sites(const int32_t *r, int64_t n, int32_t m, int32_t *out) {
     for (int64_t i = 0; i < n; ++i) out[i] = wrap_site(r[i], m);
 }
+
+// The matrix-core kernel's launch shape for K configurations (160 KB of LDS): {threads,
+// workgroups per configuration, configurations per launch}; false if it is not taken.
+extern "C" int mfma_shape(int lattice, const int *L, int M, int S, int64_t K, int64_t *out) {
+    pyhea_lattice lat{};
+    lat.lattice = lattice;
+    for (int a = 0; a < 3; ++a) lat.L[a] = L[a];
+    lat.n_species = M;
+    lat.n_shells = S;
+    Geometry g;
+    std::string err;
+    MfmaDesc md;
+    if (build_geometry(&lat, &g, &err) != PYHEA_OK || !fill_mfma_desc(g, 160 * 1024, K, &md)) return 0;
+    out[0] = md.threads;
+    out[1] = md.nchunks;
+    out[2] = md.step;
+    return 1;
+}

@@ -133,8 +133,11 @@ def test_fixed_scratch_limit_is_the_same_for_every_kernel():
     assert all(a == b for a, b in got) and not got[0][0] and not got[1][0] and got[2][0]
 
 
-@pytest.mark.parametrize("lattice,L,M,S", [(orc.FCC, (120, 120, 120), 5, 3), (orc.FCC, (120, 120, 120), 4, 3),
-                                           (orc.FCC, (60, 511, 60), 5, 4), (orc.BCC, (190, 190, 190), 5, 3)])
+LARGE = [(orc.FCC, (120, 120, 120), 5, 3), (orc.FCC, (120, 120, 120), 4, 3), (orc.FCC, (60, 511, 60), 5, 4),
+         (orc.BCC, (150, 150, 150), 5, 3)]
+
+
+@pytest.mark.parametrize("lattice,L,M,S", LARGE)
 @pytest.mark.parametrize("fractions", [(0.01, 0.01, 0.01, 0.96, 0.01), (0.05, 0.05, 0.05, 0.8, 0.05)])
 def test_large_cells(lattice, L, M, S, fractions):
     """N z beyond 2^27: 64 quarter units a pair are more than 32 bits hold."""
@@ -171,3 +174,20 @@ def test_an_invalid_id_anywhere(lattice, L, step):
     torch.cuda.synchronize()
     nan = torch.isnan(SF).all(dim=1)
     assert nan[:-1].all() and not nan[-1]
+
+
+def test_more_configurations_than_one_grid_holds():
+    """2^24 workgroups of 256 threads are one too many for a launch."""
+    lattice, L, M, S, K = orc.FCC, (3, 3, 3), 4, 1, 2**24 + 9
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    sp = torch.randint(0, M, (K, orc.n_sites(lattice, L)), dtype=torch.int8, device="cuda", generator=g)
+    got = [torch.zeros((K, S, M, M), dtype=torch.int32, device="cuda") for _ in range(2)]
+    pb.pyhea_sro_eval_batch(lattice, L, M, S, sp, got[0])
+    pb.pyhea_tune_force_eval(1)
+    try:
+        pb.pyhea_sro_eval_batch(lattice, L, M, S, sp, got[1])
+    finally:
+        pb.pyhea_tune_force_eval(-1)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])

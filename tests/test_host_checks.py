@@ -33,3 +33,27 @@ def test_decoded_sites_stay_in_the_box(m):
     out = np.empty_like(r)
     host_checks.lib().wrap_sites(_p(r), ctypes.c_int64(len(r)), m, _p(out))
     np.testing.assert_array_equal(out, r.astype(np.int64) % m)
+
+
+@pytest.mark.parametrize("lattice,L,M,S", [(0, (3, 3, 3), 4, 1), (0, (1, 2, 3), 4, 1), (0, (12, 12, 12), 5, 3),
+                                           (0, (20, 20, 20), 5, 3), (1, (3, 3, 3), 4, 1), (1, (16, 16, 16), 5, 3),
+                                           (0, (40, 40, 40), 4, 2)])
+@pytest.mark.parametrize("K", [8, 2**20, 2**24 + 8, 2**27])
+def test_one_launch_is_less_than_2_32_threads(lattice, L, M, S, K):
+    out = np.zeros(3, np.int64)
+    assert host_checks.lib().mfma_shape(lattice, _p(np.array(L, np.int32)), M, S, ctypes.c_int64(K), _p(out))
+    threads, nchunks, step = (int(v) for v in out)
+    assert step >= 8 and step % 8 == 0
+    assert step * nchunks * threads < 2**32
+
+
+def test_the_evaluation_tests_run_on_the_matrix_cores():
+    """What test_gpu_mfma_eval.py evaluates is counted by the kernel that it is about."""
+    import test_gpu_mfma_eval as t
+
+    def taken(lattice, L, M, S, K):
+        return host_checks.lib().mfma_shape(lattice, _p(np.array(L, np.int32)), M, S, ctypes.c_int64(K),
+                                            _p(np.zeros(3, np.int64)))
+
+    assert all(taken(*c) for c in t.CASES)
+    assert all(taken(*c, 1) for c in t.LARGE)
