@@ -86,7 +86,7 @@ struct FinishLds {
     double lrow[kMaxShells * 5];
 };
 constexpr int kFinishThreads = 128;   // S M^2 <= 100 entries at once: 6,500 clocks, 11,000 by one wavefront
-// The workgroup's first two wavefronts (all that are left of it) call it.
+// The whole workgroup calls it, for its barriers; the first two wavefronts do the work.
 template <class Sum>
 __device__ __forceinline__ void finish(const Sum *F, bool bad, const MfmaDesc &md, FinishLds<Sum> &l, int32_t *cnt,
                                        int32_t *bad_out, const double *tw, double *S_F) {
@@ -504,7 +504,6 @@ count_mfma_kernel(MfmaDesc md, int64_t K, const int8_t *__restrict__ species, in
         if (tid == 0) out[kMfmaGroups * 16] = sh.bad;
         return;
     }
-    if (tid >= kFinishThreads) return;
     const int E = md.S * md.M * md.M;
     finish(sh.F, sh.bad != 0, md, sh.fin, counts + kc * (int64_t)E, bad_out + kc, tw, S_F ? S_F + 2 * kc : nullptr);
 }
