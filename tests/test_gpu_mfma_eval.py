@@ -133,14 +133,14 @@ def test_fixed_scratch_limit_is_the_same_for_every_kernel():
     assert all(a == b for a, b in got) and not got[0][0] and not got[1][0] and got[2][0]
 
 
-LARGE = [(orc.FCC, (120, 120, 120), 5, 3), (orc.FCC, (120, 120, 120), 4, 3), (orc.FCC, (60, 511, 60), 5, 4),
-         (orc.BCC, (150, 150, 150), 5, 3)]
+LARGE = [(orc.FCC, (200, 200, 20), 5, 3), (orc.FCC, (60, 511, 60), 5, 4), (orc.FCC, (128, 511, 32), 5, 3),
+         (orc.FCC, (128, 511, 32), 4, 3)]
 
 
 @pytest.mark.parametrize("lattice,L,M,S", LARGE)
 @pytest.mark.parametrize("fractions", [(0.01, 0.01, 0.01, 0.96, 0.01), (0.05, 0.05, 0.05, 0.8, 0.05)])
 def test_large_cells(lattice, L, M, S, fractions):
-    """N z beyond 2^27: 64 quarter units a pair are more than 32 bits hold."""
+    """N z of 2^26 to 2^28: 64 quarter units a pair are more than 32 bits hold."""
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
     p = torch.tensor(fractions[5 - M:], device="cuda")

@@ -40,9 +40,9 @@ def test_decoded_sites_stay_in_the_box(m):
                                            (0, (40, 40, 40), 4, 2)])
 @pytest.mark.parametrize("K", [8, 2**20, 2**24 + 8, 2**27])
 def test_one_launch_is_less_than_2_32_threads(lattice, L, M, S, K):
-    out = np.zeros(3, np.int64)
+    out = np.zeros(5, np.int64)
     assert host_checks.lib().mfma_shape(lattice, _p(np.array(L, np.int32)), M, S, ctypes.c_int64(K), _p(out))
-    threads, nchunks, step = (int(v) for v in out)
+    threads, nchunks, step = (int(v) for v in out[:3])
     assert step >= 8 and step % 8 == 0
     assert step * nchunks * threads < 2**32
 
@@ -52,8 +52,11 @@ def test_the_evaluation_tests_run_on_the_matrix_cores():
     import test_gpu_mfma_eval as t
 
     def taken(lattice, L, M, S, K):
-        return host_checks.lib().mfma_shape(lattice, _p(np.array(L, np.int32)), M, S, ctypes.c_int64(K),
-                                            _p(np.zeros(3, np.int64)))
+        out = np.zeros(5, np.int64)
+        ok = host_checks.lib().mfma_shape(lattice, _p(np.array(L, np.int32)), M, S, ctypes.c_int64(K), _p(out))
+        # (large cells with one row per workgroup, or in many workgroups, go to the bit-sliced
+        # kernel if that covers them)
+        return ok and (out[3] > 1 and out[1] <= 128 or np.prod(L) * (4, 2)[lattice] <= 1200000 or not out[4])
 
     assert all(taken(*c) for c in t.CASES)
     assert all(taken(*c, 1) for c in t.LARGE)
