@@ -366,52 +366,73 @@ __device__ __forceinline__ int32_t site_at(const EvalDesc &ed, int x, int y, int
     return (((z >> 1) * ed.Ly + (y >> 1)) * ed.Lx + (x >> 1)) * ed.A + b;
 }
 
+// What no swap changes, made once per workgroup: R, the targets, the old terms.
+struct TrialTables {
+    int64_t n[kMaxSpecies];
+    int32_t off[kMaxOffsets], cnt[kMaxShells * kMaxSpecies * kMaxSpecies];
+    double R[kMaxShells * kMaxSpecies * kMaxSpecies], t[kMaxShells * kMaxSpecies * kMaxSpecies];
+    double old_sq[kMaxShells * kMaxSpecies * kMaxSpecies], weight[kMaxShells];
+};
+
+// Fills l; false if an id is invalid or a species absent (*status, in host memory, is then 1
+// and nothing else is to be written; else 0).
+__device__ __forceinline__ bool trial_tables(TrialTables &l, const EvalDesc &ed, const SmallTable &tw,
+                                             const int32_t *counts, const int32_t *bad, int32_t *status) {
+    const int M = ed.M, E = ed.S * M * M;
+    const int tid = (int)threadIdx.x, nthreads = (int)blockDim.x;
+    if (tid < M) {
+        int64_t r = 0;
+        for (int j = 0; j < M; ++j) r += counts[tid * M + j];
+        l.n[tid] = r / ed.z0;
+    }
+    for (int i = tid; i < ed.Z; i += nthreads) __builtin_memcpy(&l.off[i], ed.off[i], 4);
+    if (tid < ed.S) l.weight[tid] = tw.v[E + tid];
+    __syncthreads();
+    bool ok = *bad == 0;
+    for (int i = 0; i < M; ++i) ok = ok && l.n[i] > 0;
+    if (blockIdx.x == 0 && tid == 0) *status = ok ? 0 : 1;
+    if (!ok) return false;
+    for (int e = tid; e < E; e += nthreads) {
+        const int k = e / (M * M), i = (e / M) % M, j = e % M;
+        l.cnt[e] = counts[e];
+        l.t[e] = tw.v[e];
+        l.R[e] = (double)ed.N / (double)(l.n[i] * l.n[j] * (int64_t)ed.zk[k]);
+        const double a0 = 1.0 - (double)counts[e] * l.R[e];
+        const double d0 = a0 - tw.v[e];
+        l.old_sq[e] = d0 * d0;
+    }
+    __syncthreads();
+    return true;
+}
+
+// dN_ij of a shell for swapping species a != b, from the changes D of the neighbours'
+// species (of the site that becomes a, less those of the site that becomes b).
+__device__ __forceinline__ int trial_dn(int i, int j, int a, int b, int Da, int Db, int Di, int Dj) {
+    if (i == a) return j == a ? 2 * Da : (j == b ? Db - Da : Dj);
+    if (i == b) return j == b ? -2 * Db : (j == a ? Db - Da : -Dj);
+    return j == a ? Di : (j == b ? -Di : 0);
+}
+
 // dS and dN of given swaps against one configuration (no swap applied).  Half a
 // wavefront takes a pair: its lanes read the neighbours of both sites at once and add up
 // the change of the rows of species a and b in LDS; then a lane per row of a shell sums its
-// M terms and one lane the rows, in the order of Eq. 3.  What no swap changes (R, the old
-// terms) is made once per workgroup.  A lane per pair took 83 us for 4,096 pairs on FCC
-// 20^3, 5 species, 3 shells: 42 dependent reads twice, row counters in scratch memory and
-// 75 divisions per pair; now the call, count included, takes 59 us of 273.  Bound by the
-// latency of those steps and the launches.
-// *status (host memory): 1 if an id is invalid or a species absent, and nothing else is
-// written then.
+// M terms and one lane the rows, in the order of Eq. 3.  A lane per pair took 83 us for
+// 4,096 pairs on FCC 20^3, 5 species, 3 shells: 42 dependent reads twice, row counters in
+// scratch memory and 75 divisions per pair; now the call, count included, takes 59 us of
+// 273.  Bound by the latency of those steps and the launches.
 constexpr int kTrialLanes = 32;      // a lane for each of S M rows
 constexpr int kTrialThreads = 256;
 __global__ void __launch_bounds__(kTrialThreads)
 trial_eval_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, const int32_t *__restrict__ counts,
                   const int32_t *__restrict__ bad, int64_t n_pairs, const int32_t *__restrict__ pairs,
                   double *__restrict__ dS_out, int32_t *__restrict__ dN_out, int32_t *__restrict__ status) {
-    constexpr int kGroups = kTrialThreads / kTrialLanes, kMaxE = kMaxShells * kMaxSpecies * kMaxSpecies;
-    __shared__ int64_t n[kMaxSpecies];
-    __shared__ int32_t off[kMaxOffsets], cnt[kMaxE];
-    __shared__ double R[kMaxE], t[kMaxE], old_sq[kMaxE], weight[kMaxShells];
+    constexpr int kGroups = kTrialThreads / kTrialLanes;
+    __shared__ TrialTables l;
     __shared__ int32_t D_all[kGroups][kMaxShells][kMaxSpecies];
     __shared__ double row_all[kGroups][kMaxShells * kMaxSpecies];
     const int M = ed.M, E = ed.S * M * M;
     const int tid = (int)threadIdx.x;
-    if (tid < M) {
-        int64_t r = 0;
-        for (int j = 0; j < M; ++j) r += counts[tid * M + j];
-        n[tid] = r / ed.z0;
-    }
-    for (int i = tid; i < ed.Z; i += kTrialThreads) __builtin_memcpy(&off[i], ed.off[i], 4);
-    if (tid < ed.S) weight[tid] = tw.v[E + tid];
-    __syncthreads();
-    bool ok = *bad == 0;
-    for (int i = 0; i < M; ++i) ok = ok && n[i] > 0;
-    if (blockIdx.x == 0 && tid == 0) *status = ok ? 0 : 1;
-    if (!ok) return;
-    for (int e = tid; e < E; e += kTrialThreads) {
-        const int k = e / (M * M), i = (e / M) % M, j = e % M;
-        cnt[e] = counts[e];
-        t[e] = tw.v[e];
-        R[e] = (double)ed.N / (double)(n[i] * n[j] * (int64_t)ed.zk[k]);
-        const double a0 = 1.0 - (double)counts[e] * R[e];
-        const double d0 = a0 - tw.v[e];
-        old_sq[e] = d0 * d0;
-    }
-    __syncthreads();
+    if (!trial_tables(l, ed, tw, counts, bad, status)) return;
     const int group = tid / kTrialLanes, lane = tid % kTrialLanes;
     int32_t(&D)[kMaxShells][kMaxSpecies] = D_all[group];
     double *row = row_all[group];
@@ -434,7 +455,7 @@ trial_eval_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, con
                 basis_bits(ed.A, c.b, bx, by, bz);
                 basis_bits(ed.A, d.b, ex, ey, ez);
                 for (int i = lane; i < ed.Z; i += kTrialLanes) {
-                    const int32_t o = off[i];
+                    const int32_t o = l.off[i];
                     const int ox = (int8_t)o, oy = (int8_t)(o >> 8), oz = (int8_t)(o >> 16), k = o >> 24;
                     const int32_t rp = site_at(ed, 2 * c.cx + bx + ox, 2 * c.cy + by + oy, 2 * c.cz + bz + oz);
                     const int32_t rq = site_at(ed, 2 * d.cx + ex + ox, 2 * d.cy + ey + oy, 2 * d.cz + ez + oz);
@@ -449,19 +470,12 @@ trial_eval_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, con
             const int Da = D[k][a], Db = D[k][b], Di = D[k][i];
             double rowsum = 0.0;
             for (int j = 0; j < M; ++j) {
-                const int Dj = D[k][j];
-                int dn = 0;
-                if (a != b) {
-                    if (i == a) dn = j == a ? 2 * Da : (j == b ? Db - Da : Dj);
-                    else if (i == b) dn = j == b ? -2 * Db : (j == a ? Db - Da : -Dj);
-                    else if (j == a) dn = Di;
-                    else if (j == b) dn = -Di;
-                }
+                const int dn = a != b ? trial_dn(i, j, a, b, Da, Db, Di, D[k][j]) : 0;
                 const int e = lane * M + j;
                 if (dN_out) dN_out[u * E + e] = dn;
-                const double a1 = 1.0 - (double)(cnt[e] + dn) * R[e];
-                const double d1 = a1 - t[e];
-                rowsum = rowsum + (d1 * d1 - old_sq[e]);
+                const double a1 = 1.0 - (double)(l.cnt[e] + dn) * l.R[e];
+                const double d1 = a1 - l.t[e];
+                rowsum = rowsum + (d1 * d1 - l.old_sq[e]);
             }
             row[lane] = rowsum;
         }
@@ -471,10 +485,98 @@ trial_eval_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, con
             for (int k = 0; k < ed.S; ++k) {
                 double dQ = 0.0;
                 for (int i = 0; i < M; ++i) dQ = dQ + row[k * M + i];
-                acc = acc + weight[k] * dQ;
+                acc = acc + l.weight[k] * dQ;
             }
             dS_out[u] = valid ? acc : __longlong_as_double(0x7ff8000000000000ll);
         }
+    }
+}
+
+// The same by a lane per pair, for many pairs: bound by the issue of instructions, where
+// half a wavefront per pair leaves most lanes idle in turn.  dN goes out row by row of a
+// shell, M^2 lanes per pair, from the pairs' histograms in LDS: a lane that writes its own
+// pair's E entries touches a line per entry.  2,000,000 pairs on FCC 20^3, 5 species,
+// 3 shells, half a wavefront per pair -> here: 1,304 -> 583 us, with dN 1,353 -> 848.
+__global__ void __launch_bounds__(kTrialThreads)
+trial_eval_many_kernel(EvalDesc ed, SmallTable tw, const int8_t *__restrict__ sp, const int32_t *__restrict__ counts,
+                       const int32_t *__restrict__ bad, int64_t n_pairs, const int32_t *__restrict__ pairs,
+                       double *__restrict__ dS_out, int32_t *__restrict__ dN_out, int32_t *__restrict__ status) {
+    __shared__ TrialTables l;
+    __shared__ uint64_t hp_all[kTrialThreads], hq_all[kTrialThreads];
+    __shared__ int32_t ab_all[kTrialThreads];   // a | b << 8, or -1: no such pair
+    const int M = ed.M, E = ed.S * M * M, M2 = M * M;
+    const int tid = (int)threadIdx.x, lane = tid % kWave, wave0 = tid - lane;
+    if (!trial_tables(l, ed, tw, counts, bad, status)) return;
+    // this lane's entry (oi, oj) of the pairs that it writes, and which of them
+    const int at_once = kWave / M2, sub = lane / M2, oe = lane - sub * M2, oi = oe / M, oj = oe - oi * M;
+    const auto diff = [](uint64_t hp, uint64_t hq, int j) {
+        return (int)((hq >> (5 * j)) & 31u) - (int)((hp >> (5 * j)) & 31u);
+    };
+    // every lane makes the same number of turns, for the barriers
+    for (int64_t u0 = (int64_t)blockIdx.x * kTrialThreads; u0 < n_pairs; u0 += (int64_t)gridDim.x * kTrialThreads) {
+        const int64_t u = u0 + tid;
+        const bool here = u < n_pairs;
+        const int32_t p = here ? pairs[2 * u] : -1, q = here ? pairs[2 * u + 1] : -1;
+        const bool valid = here && p >= 0 && q >= 0 && (uint32_t)p < ed.N && (uint32_t)q < ed.N;
+        const int a = valid ? sp[p] : 0, b = valid ? sp[q] : 0;
+        const SiteCoord c = site_coord(valid ? (uint32_t)p : 0u, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
+        const SiteCoord d = site_coord(valid ? (uint32_t)q : 0u, ed.lgA, ed.Lx, ed.Ly, ed.inv_Lx, ed.inv_Ly);
+        int bx, by, bz, ex, ey, ez;
+        basis_bits(ed.A, c.b, bx, by, bz);
+        basis_bits(ed.A, d.b, ex, ey, ez);
+        if (dN_out) ab_all[tid] = valid ? a | b << 8 : -1;
+        double acc = 0.0;
+        int t = 0;
+        for (int k = 0; k < ed.S; ++k) {
+            // neighbours of p and of q by species, the other site left out: 5-bit fields (z_k <= 24)
+            uint64_t hp = 0, hq = 0;
+            const int t1 = t + ed.zk[k];
+            if (a != b)
+                for (int i = t; i < t1; ++i) {
+                    const int32_t o = l.off[i];
+                    const int ox = (int8_t)o, oy = (int8_t)(o >> 8), oz = (int8_t)(o >> 16);
+                    const int32_t rp = site_at(ed, 2 * c.cx + bx + ox, 2 * c.cy + by + oy, 2 * c.cz + bz + oz);
+                    const int32_t rq = site_at(ed, 2 * d.cx + ex + ox, 2 * d.cy + ey + oy, 2 * d.cz + ez + oz);
+                    const int vp = sp[rp], vq = sp[rq];
+                    hp += rp != q ? 1ull << (5 * vp) : 0ull;
+                    hq += rq != p ? 1ull << (5 * vq) : 0ull;
+                }
+            t = t1;
+            if (dN_out) {
+                hp_all[tid] = hp;
+                hq_all[tid] = hq;
+                __syncthreads();
+                for (int x0 = 0; x0 < kWave; x0 += at_once) {
+                    const int x = wave0 + x0 + sub;
+                    if (sub >= at_once || x0 + sub >= kWave) continue;
+                    const int32_t ab = ab_all[x];
+                    if (ab < 0) continue;
+                    const int oa = ab & 0xFF, ob = ab >> 8;
+                    const uint64_t xp = hp_all[x], xq = hq_all[x];
+                    const int dn = oa != ob ? trial_dn(oi, oj, oa, ob, diff(xp, xq, oa), diff(xp, xq, ob),
+                                                       diff(xp, xq, oi), diff(xp, xq, oj))
+                                            : 0;
+                    dN_out[(u0 + x) * E + k * M2 + oe] = dn;
+                }
+                __syncthreads();
+            }
+            const int Da = diff(hp, hq, a), Db = diff(hp, hq, b);
+            double dQ = 0.0;
+            for (int i = 0; i < M; ++i) {
+                const int Di = diff(hp, hq, i);
+                double rowsum = 0.0;
+                for (int j = 0; j < M; ++j) {
+                    const int dn = a != b ? trial_dn(i, j, a, b, Da, Db, Di, diff(hp, hq, j)) : 0;
+                    const int e = (k * M + i) * M + j;
+                    const double a1 = 1.0 - (double)(l.cnt[e] + dn) * l.R[e];
+                    const double d1 = a1 - l.t[e];
+                    rowsum = rowsum + (d1 * d1 - l.old_sq[e]);
+                }
+                dQ = dQ + rowsum;
+            }
+            acc = acc + l.weight[k] * dQ;
+        }
+        if (here) dS_out[u] = valid ? acc : __longlong_as_double(0x7ff8000000000000ll);
     }
 }
 
@@ -588,15 +690,23 @@ hipError_t launch_copy_rows(const int *rows, int count, int64_t N, const int8_t 
     return hipSuccess;
 }
 
+// Pairs from which a lane per pair is faster, without and with dN.  us per call, half a
+// wavefront / a lane per pair: without dN 65,536 pairs FCC 20^3, 8 species, 4 shells 275 /
+// 290, 5 species, 3 shells 103 / 112, BCC 31^3, 3 species, 4 shells 104 / 115, FCC 40^3, 4
+// species, 2 shells 92 / 85; 130,000 pairs 346 / 300, 144 / 119, 140 / 123, 120 / 88.  With dN
+// 130,000 pairs FCC 20^3, 5 species, 4 shells 154 / 182, 3 shells 151 / 152; 260,000 pairs 8
+// species, 4 shells 497 / 455, 5 species, 3 shells 231 / 191.
+constexpr int64_t kTrialMany = 80000, kTrialManyDN = 200000;
 hipError_t launch_trial_eval(const EvalDesc &ed, const SmallTable &tw, const int8_t *species, const int32_t *counts,
                              const int32_t *bad, int64_t n_pairs, const int32_t *pairs, double *dS, int32_t *dN,
                              int32_t *status, hipStream_t stream) {
     static_assert(kMaxShells * kMaxSpecies == kTrialLanes, "a lane per row of D");
-    const int per = kTrialThreads / kTrialLanes;
+    const bool many = n_pairs >= (dN ? kTrialManyDN : kTrialMany);
+    const int per = many ? kTrialThreads : kTrialThreads / kTrialLanes;
     // at most 8 workgroups per CU, each with many pairs: their tables are made once
     const int blocks = (int)std::min<int64_t>(std::max<int64_t>(1, (n_pairs + per - 1) / per), 2048);
-    hipLaunchKernelGGL(trial_eval_kernel, dim3(blocks), dim3(kTrialThreads), 0, stream, ed, tw, species, counts, bad,
-                       n_pairs, pairs, dS, dN, status);
+    hipLaunchKernelGGL(many ? trial_eval_many_kernel : trial_eval_kernel, dim3(blocks), dim3(kTrialThreads), 0, stream,
+                       ed, tw, species, counts, bad, n_pairs, pairs, dS, dN, status);
     return hipGetLastError();
 }
 

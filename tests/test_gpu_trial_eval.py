@@ -64,3 +64,37 @@ def test_refused_configuration_writes_nothing(n, value):
         pb.pyhea_trial_eval(orc.FCC, (4, 4, 4), M, S, torch.from_numpy(sp).cuda(), np.zeros((S, M, M)), np.ones(S),
                             pairs, dS, dN)
     assert (dS == 7).all() and (dN == 7).all()
+
+
+@pytest.mark.parametrize("lattice,L,M,S", [
+    (orc.FCC, (3, 3, 3), 8, 4), (orc.FCC, (2, 2, 3), 2, 2), (orc.BCC, (3, 3, 3), 7, 4), (orc.FCC, (4, 4, 4), 5, 3),
+    (orc.BCC, (5, 4, 3), 3, 2), (orc.FCC, (6, 5, 4), 4, 1), (orc.FCC, (20, 20, 20), 6, 3),
+])
+@pytest.mark.parametrize("n,with_dN", [(80000, False), (80037, False), (200000, True), (200191, True), (600001, True)])
+def test_many_pairs_equal_few(lattice, L, M, S, n, with_dN):
+    """From 80,000 pairs (200,000 with dN) a lane takes a pair: the results of calls with fewer."""
+    N = orc.n_sites(lattice, L)
+    sp = wl.iid_configs(N, M, 1, seed=M)[0]
+    sp[:M] = np.arange(M)
+    sp = torch.from_numpy(sp).cuda()
+    rng = np.random.default_rng(n)
+    tgt, w = rng.uniform(-0.2, 0.2, (S, M, M)), rng.uniform(0.1, 1.0, S)
+    pairs = rng.integers(0, N, size=(n, 2)).astype(np.int32)
+    pairs[3::1000, 1] = pairs[3::1000, 0]    # a site with itself
+    pairs[4::1000] = [0, 1]                  # neighbours
+    pairs[5::1000] = [-1, 0]
+    pairs[n - 1] = [0, N]
+    pairs = torch.from_numpy(pairs).cuda()
+
+    def call(pairs, guard):
+        dS = torch.full((len(pairs) + guard,), 7.0, dtype=torch.float64, device="cuda")
+        dN = torch.full((len(pairs) + guard, S, M, M), 7, dtype=torch.int32, device="cuda")
+        pb.pyhea_trial_eval(lattice, L, M, S, sp, tgt, w, pairs, dS[:len(pairs)], dN[:len(pairs)] if with_dN else None)
+        assert (dS[len(pairs):] == 7).all() and (dN[len(pairs):] == 7).all()
+        return dS[:len(pairs)], dN[:len(pairs)]
+
+    dS, dN = call(pairs, 300)
+    few = [call(p, 0) for p in pairs.split(50000)]
+    want_S, want_N = torch.cat([f[0] for f in few]), torch.cat([f[1] for f in few])
+    assert torch.equal(dS.view(torch.int64), want_S.view(torch.int64)) and torch.equal(dN, want_N)
+    assert torch.isnan(dS[5::1000]).all() and torch.isnan(dS[n - 1])
