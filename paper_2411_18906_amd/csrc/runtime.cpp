@@ -856,10 +856,12 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     // a quiet stretch.  The rounds of a call are launched without waiting; a round
     // that finds nothing to do costs its launches only, and a call whose chains
     // are not done after them goes on in further rounds (below).
-    int64_t longest = 0;
+    int64_t longest = 0;   // of the chains that can leave kMinScan steps to a scan
     for (int c = 0; c < n; ++c) {
         const int64_t B = jobs[c].params.cand_per_step;
-        longest = std::max(longest, (jobs[c].params.n_trials + B - 1) / B);
+        const int depth = jobs[c].params.depth_limit;
+        if (depth == 0 || depth >= kQuietSteps + kMinScan)
+            longest = std::max(longest, (jobs[c].params.n_trials + B - 1) / B);
     }
     const bool wide = n <= kWideChains && longest >= kWideSteps;
     const int rounds = !wide ? 0 : longest >= kManySteps ? kRoundsLong : kRoundsShort;

@@ -80,3 +80,10 @@ def test_several_chains_in_one_call():
             np.testing.assert_array_equal(fin[off[i]:off[i + 1]], sp_o, err_msg=f"chain {i}")
             for k in ("trials", "null_trials", "commits", "steps", "S"):
                 assert stats[i][k] == st_o[k], (i, k)
+
+
+@pytest.mark.parametrize("depth", [4, 63, 64, 65, 80])
+def test_depth_limit_around_the_first_scan(depth):
+    """A chain scans if its depth limit leaves the scan's least steps (64 and more)."""
+    test_quiet_chain_equals_oracle((wl.FCC, (5, 5, 5), 5, 3, 10**6, 64, 0, depth, 0.0, True, -1))
+    test_quiet_chain_equals_oracle((wl.BCC, (6, 5, 4), 4, 2, 10**6, 100, 0, depth, 0.0, False, -1))
