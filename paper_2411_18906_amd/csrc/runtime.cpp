@@ -162,17 +162,6 @@ pyhea_status check_params(const pyhea_mc_params *p) {
     return PYHEA_OK;
 }
 
-bool species_totals(const Geometry &g, const int64_t *counts, int64_t *n) {
-    bool ok = true;
-    for (int i = 0; i < g.M; ++i) {
-        int64_t r = 0;
-        for (int j = 0; j < g.M; ++j) r += counts[i * g.M + j];
-        n[i] = r / g.z[0];
-        ok = ok && n[i] > 0;
-    }
-    return ok;
-}
-
 void ratio_table(const Geometry &g, const int64_t *n, double *R) {
     for (int k = 0; k < g.S; ++k)
         for (int i = 0; i < g.M; ++i)
