@@ -10,7 +10,6 @@ namespace pyhea {
 constexpr int kMaxLookahead = 8;   // pyhea_tune_force_lookahead: 1 = step by step, more = quiet steps in windows
 constexpr int kRing = 8;           // steps whose candidates are drawn ahead
 constexpr int kChunk = 32;         // members of a commit chunk at most (half a wavefront)
-constexpr int kMinScan = 48;       // steps left below which a quiet chain finishes by itself
 constexpr int kMaxWaves = 8;       // wavefronts of a chain's workgroup at most
 
 // LDS of the MC kernel without the species store: CH = members of a commit chunk.

@@ -566,6 +566,8 @@ __device__ __forceinline__ bool scan_item(const Chain &d, const Ent *ent, const 
     return ballot64(imp) != 0;
 }
 
+constexpr int kMinScan = 48;    // steps left below which a quiet chain finishes by itself
+
 // kG: slot groups of 64 (1, or kMaxB / 64 for any B)
 template <int kStore, int M, int kG>
 __global__ void __launch_bounds__(kMaxWaves * kWave, 4) mc_kernel(const ChainDesc *__restrict__ descs, int32_t max_steps, int32_t K,

@@ -674,14 +674,23 @@ hipError_t record_plan(ChainPlan *p, Work &work) {
     return e;
 }
 
-// Calls that scan (run_chains): chains at most, steps of the longest at least.
-// Below kWideSteps the rounds' launches cost more than the scan saves (us per call
-// without / with: 130 steps FCC 4^3 260 / 273, FCC 8^3 436 / 467, BCC 16^3 393 / 417; 200
-// steps 303 / 310, 499 / 552, 447 / 472, FCC 20^3 801 / 793; 300 steps 345 / 295, 572 / 650,
-// 492 / 467, 920 / 904); many chains keep the CUs busy by themselves, and the windows of
-// more chains than kWideChains would wait for the slowest chain of each round.
+// Calls that scan (run_chains): chains at most, steps of the longest and its depth limit at
+// least.  A round costs its launches, and every chain of the call waits for the slowest one
+// of the round, so both limits grow with the number of chains.  us per call without / with:
+//   1 chain: 130 steps FCC 4^3 260 / 273, FCC 8^3 436 / 467; 313 steps FCC 4^3 401 / 331, FCC
+//     8^3 1,121 / 1,106, BCC 6^3 841 / 926, FCC 20^3 2,528 / 2,553, BCC 20^3 975 / 946; 1,563
+//     steps FCC 4^3 1,057 / 407, FCC 20^3 5,204 / 4,730.
+//   2 chains: 469 steps FCC 6^3 1,320 / 1,483, BCC 6^3 1,225 / 1,311.
+//   4 chains: 313 steps FCC 6^3 1,106 / 1,245, FCC 8^3 1,266 / 1,510, BCC 6^3 992 / 1,391; 1,563
+//     steps 2,702 / 1,803, 2,609 / 2,065, 2,461 / 1,895.
+//   16 chains: 313 steps FCC 6^3 1,146 / 1,929, BCC 20^3 1,050 / 1,412; 1,563 steps 2,749 / 2,937,
+//     1,710 / 1,433, FCC 20^3 5,316 / 5,734, FCC 4^3 1,186 / 885.
+//   Depth limits, up to 10^5 trials: 1 chain FCC 4^3 64 233 / 285, 80 335 / 345, 120 357 / 343, 200 581
+//     / 410; 4 chains FCC 6^3 80 1,448 / 1,622, 200 1,600 / 1,623, 400 1,831 / 1,619; 16 chains 200
+//     1,756 / 2,066, 400 2,760 / 2,614.
 constexpr int kWideChains = 16;
-constexpr int kWideSteps = 224;
+constexpr int kWideSteps = 224, kWideStepsMany = 360, kWideStepsChain = 70;   // one chain; several, and for each
+constexpr int kWideDepth = 60, kWideDepthChain = 20;
 // Steps without a commit after which a chain goes to the scan: a round (two
 // launches, the LDS fills, one evaluation) costs about as much as these steps on
 // one CU.
@@ -845,14 +854,14 @@ pyhea_status run_chains(std::vector<ChainJob> &jobs, pyhea_mc_stats *stats,
     // a quiet stretch.  The rounds of a call are launched without waiting; a round
     // that finds nothing to do costs its launches only, and a call whose chains
     // are not done after them goes on in further rounds (below).
-    int64_t longest = 0;   // of the chains that can leave kMinScan steps to a scan
+    int64_t longest = 0;   // of the chains without a depth limit that ends them before a scan pays
     for (int c = 0; c < n; ++c) {
         const int64_t B = jobs[c].params.cand_per_step;
         const int depth = jobs[c].params.depth_limit;
-        if (depth == 0 || depth >= kQuietSteps + kMinScan)
+        if (depth == 0 || depth >= kWideDepth + kWideDepthChain * n)
             longest = std::max(longest, (jobs[c].params.n_trials + B - 1) / B);
     }
-    const bool wide = n <= kWideChains && longest >= kWideSteps;
+    const bool wide = n <= kWideChains && longest >= (n == 1 ? kWideSteps : kWideStepsMany + kWideStepsChain * n);
     const int rounds = !wide ? 0 : longest >= kManySteps ? kRoundsLong : kRoundsShort;
     std::vector<size_t> o_image(n, 0), o_nulls(n, 0);
     if (wide)

@@ -82,8 +82,28 @@ def test_several_chains_in_one_call():
                 assert stats[i][k] == st_o[k], (i, k)
 
 
-@pytest.mark.parametrize("depth", [4, 63, 64, 65, 80])
+@pytest.mark.parametrize("depth", [4, 63, 64, 79, 80, 81, 120])
 def test_depth_limit_around_the_first_scan(depth):
-    """A chain scans if its depth limit leaves the scan's least steps (64 and more)."""
+    """A single chain scans from a depth limit of 80 on."""
     test_quiet_chain_equals_oracle((wl.FCC, (5, 5, 5), 5, 3, 10**6, 64, 0, depth, 0.0, True, -1))
     test_quiet_chain_equals_oracle((wl.BCC, (6, 5, 4), 4, 2, 10**6, 100, 0, depth, 0.0, False, -1))
+
+
+@pytest.mark.parametrize("n,steps", [(1, 223), (1, 224), (2, 499), (2, 500), (16, 1479), (16, 1480), (17, 3000)])
+@pytest.mark.parametrize("depth", [0, 99, 100, 380])
+def test_calls_around_the_least_steps(n, steps, depth):
+    """The least steps and depth limit of a call that scans grow with its chains."""
+    lattice, L, M, S, B = wl.FCC, (3, 4, 3), 4, 2, 32
+    jobs = [_problem(lattice, L, M, S, 30 + i, False) for i in range(n)]
+    N = len(jobs[0][0])
+    pars = [pb.make_params(9, i, steps * B if i == 0 else 50 * B, B, 0, depth, 0.0) for i in range(n)]
+    d = torch.from_numpy(np.concatenate([j[0] for j in jobs])).cuda()
+    stats = pb.pyhea_mc_batch([(lattice, L, M, S, j[1], j[2]) for j in jobs], d, np.arange(n + 1) * N, pars)
+    fin = d.cpu().numpy()
+    for i in range(min(n, 3)):
+        sp, tgt, w = jobs[i]
+        sp_o, _, st_o, _ = orc.mc_run(lattice, L, M, S, tgt, w, sp, seed=9, chain_id=i,
+                                      n_trials=(steps if i == 0 else 50) * B, B=B, depth_limit=depth)
+        np.testing.assert_array_equal(fin[i * N:(i + 1) * N], sp_o)
+        for k in ("trials", "null_trials", "commits", "steps", "S"):
+            assert stats[i][k] == st_o[k], (i, k)
