@@ -568,11 +568,19 @@ __device__ __forceinline__ bool scan_item(const Chain &d, const Ent *ent, const 
 
 constexpr int kMinScan = 48;    // steps left below which a quiet chain finishes by itself
 
-// kG: slot groups of 64 (1, or kMaxB / 64 for any B)
-template <int kStore, int M, int kG>
+// kGroups: slot groups of 64 (1, or kMaxB / 64 for any B); 0: one, with few candidates a
+// step.  A window takes about as long as two to four steps by themselves, and with few
+// candidates a chain often commits after that many steps; such a chain opens windows only
+// after kFewGap quiet steps, or if as many came before its last commit.  ms for 64 chains of
+// 2,000 steps, without / with that: FCC 20^3, 1 candidate 12.6 / 8.6, 4 candidates 15.2 / 11.9;
+// BCC 10^3, 6 species, 4 shells 13.3 / 10.0; FCC 4^3, commits far apart, 2.06 / 2.05.
+constexpr int kFewGap = 8;
+template <int kStore, int M, int kGroups>
 __global__ void __launch_bounds__(kMaxWaves * kWave, 4) mc_kernel(const ChainDesc *__restrict__ descs, int32_t max_steps, int32_t K,
                                                   int32_t CH, int32_t quiet) {
     using Hist = typename HistT<(M > 6)>::type;
+    constexpr bool kFew = kGroups == 0;
+    constexpr int kG = kFew ? 1 : kGroups;
     const ChainDesc &desc = descs[blockIdx.x];
     ChainState *st = desc.state;
     if (st->done) return;
@@ -663,7 +671,7 @@ __global__ void __launch_bounds__(kMaxWaves * kWave, 4) mc_kernel(const ChainDes
     // kMinScan are left, and comes back at the first step of the scanned window
     // that holds an improving candidate (or at its end).  The steps before it
     // commit nothing: only their counters move on.
-    int quiet_run = 0;
+    int quiet_run = 0, last_gap = 0;
     if (scan_steps > 0) {
         const int adv = __builtin_amdgcn_readfirstlane(st->scan_found);
         int32_t sum = 0;
@@ -984,8 +992,10 @@ __global__ void __launch_bounds__(kMaxWaves * kWave, 4) mc_kernel(const ChainDes
         ++step;
         --steps_left;
         depth = n_commit > 0 ? 0 : depth + 1;
+        if constexpr (kFew) last_gap = n_commit > 0 ? quiet_run : last_gap;
         quiet_run = n_commit > 0 ? 0 : quiet_run + 1;
         window = n_commit > 0 || K == 1 ? 0 : nw;
+        if (kFew && max(last_gap, quiet_run) < kFewGap) window = 0;
         if (depth_limit > 0 && depth >= depth_limit) {
             stop_reason = PYHEA_STOP_DEPTH;
             done = true;
@@ -1133,9 +1143,12 @@ const void *mc_fn(int M) {
         default: return (const void *)mc_kernel<kStore, 8, kG>;
     }
 }
+// From 16 candidates a step on windows from the first quiet step measured as well: FCC 20^3
+// 11.6 ms without / 11.4 with the wait, BCC 10^3 5.9 / 5.6, FCC 4^3 1.57 / 1.58.
+constexpr int kFewB = 16;
 template <int kStore>
 const void *mc_fn(int M, int B) {
-    return B <= kWave ? mc_fn<kStore, 1>(M) : mc_fn<kStore, kMaxB / kWave>(M);
+    return B < kFewB ? mc_fn<kStore, 0>(M) : B <= kWave ? mc_fn<kStore, 1>(M) : mc_fn<kStore, kMaxB / kWave>(M);
 }
 
 int lds_fixed_bytes(int M) {

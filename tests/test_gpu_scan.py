@@ -107,3 +107,12 @@ def test_calls_around_the_least_steps(n, steps, depth):
         np.testing.assert_array_equal(fin[i * N:(i + 1) * N], sp_o)
         for k in ("trials", "null_trials", "commits", "steps", "S"):
             assert stats[i][k] == st_o[k], (i, k)
+
+
+@pytest.mark.parametrize("B", [1, 3, 15, 16])
+@pytest.mark.parametrize("lattice,L,M,S,variant", [(wl.FCC, (4, 4, 4), 4, 2, -1), (wl.FCC, (3, 4, 5), 7, 3, 1),
+                                                   (wl.BCC, (6, 5, 4), 3, 4, 2)])
+def test_few_candidates_a_step(lattice, L, M, S, variant, B):
+    """Below 16 candidates a step windows open after quiet steps only."""
+    for mode, depth, tau in ((0, 0, 0.0), (1, 0, 0.0), (0, 13, 0.0), (0, 0, -1e-6)):
+        test_quiet_chain_equals_oracle((lattice, L, M, S, 700 * B + B // 2, B, mode, depth, tau, False, variant))
