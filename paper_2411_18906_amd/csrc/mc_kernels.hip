@@ -39,8 +39,9 @@
 // registers because a descriptor load waits for L2.  FCC 40^3, 4 species, 2
 // shells (1,450 committing steps, 19.6 commits each): 14.0 us per step with one
 // wavefront per shell and 64 slots, commit walk in chunks of 16 and per-basis
-// offset tables, 6.9 us now; of it evaluation 27 %, commits 38 %, ranks and
-// conflicts 26 %.  512 chains of 250-16,000 sites: 6.1 -> 3.6 ms per call.
+// offset tables, 6.9 us now; of it evaluation 27 %, commits 39 %, ranks and
+// conflicts 29 % (clocks of the first wavefront, its waits included).  512 chains of
+// 250-16,000 sites: 6.1 -> 3.6 ms per call.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -680,16 +680,18 @@ hipError_t record_plan(ChainPlan *p, Work &work) {
 //   1 chain: 130 steps FCC 4^3 260 / 273, FCC 8^3 436 / 467; 313 steps FCC 4^3 401 / 331, FCC
 //     8^3 1,121 / 1,106, BCC 6^3 841 / 926, FCC 20^3 2,528 / 2,553, BCC 20^3 975 / 946; 1,563
 //     steps FCC 4^3 1,057 / 407, FCC 20^3 5,204 / 4,730.
-//   2 chains: 469 steps FCC 6^3 1,320 / 1,483, BCC 6^3 1,225 / 1,311.
-//   4 chains: 313 steps FCC 6^3 1,106 / 1,245, FCC 8^3 1,266 / 1,510, BCC 6^3 992 / 1,391; 1,563
-//     steps 2,702 / 1,803, 2,609 / 2,065, 2,461 / 1,895.
-//   16 chains: 313 steps FCC 6^3 1,146 / 1,929, BCC 20^3 1,050 / 1,412; 1,563 steps 2,749 / 2,937,
-//     1,710 / 1,433, FCC 20^3 5,316 / 5,734, FCC 4^3 1,186 / 885.
+//   Several, without over with, geometric mean of three mixed batches and five cells of 256
+//     to 32,000 sites (between 0.6 and 2.3 at these steps):
+//       steps      468   703   1,015  1,562  2,343
+//       2 chains   0.96  1.05  1.21   1.57   1.95
+//       4          0.84  0.91  1.04   1.36   1.66
+//       8          0.80  0.88  0.96   1.16   1.39
+//       16         0.73  0.81  0.87   1.04   1.25
 //   Depth limits, up to 10^5 trials: 1 chain FCC 4^3 64 233 / 285, 80 335 / 345, 120 357 / 343, 200 581
 //     / 410; 4 chains FCC 6^3 80 1,448 / 1,622, 200 1,600 / 1,623, 400 1,831 / 1,619; 16 chains 200
 //     1,756 / 2,066, 400 2,760 / 2,614.
 constexpr int kWideChains = 16;
-constexpr int kWideSteps = 224, kWideStepsMany = 360, kWideStepsChain = 70;   // one chain; several, and for each
+constexpr int kWideSteps = 224, kWideStepsMany = 640, kWideStepsChain = 55;   // one chain; several, and for each
 constexpr int kWideDepth = 60, kWideDepthChain = 20;
 // Steps without a commit after which a chain goes to the scan: a round (two
 // launches, the LDS fills, one evaluation) costs about as much as these steps on

@@ -82,14 +82,22 @@ def test_several_chains_in_one_call():
                 assert stats[i][k] == st_o[k], (i, k)
 
 
+@pytest.fixture
+def eager():
+    """No recorded graphs: a process keeps the first 32 structures that are called twice."""
+    pb.pyhea_tune_graphs(False)
+    yield
+    pb.pyhea_tune_graphs(True)
+
+
 @pytest.mark.parametrize("depth", [4, 63, 64, 79, 80, 81, 120])
-def test_depth_limit_around_the_first_scan(depth):
+def test_depth_limit_around_the_first_scan(depth, eager):
     """A single chain scans from a depth limit of 80 on."""
     test_quiet_chain_equals_oracle((wl.FCC, (5, 5, 5), 5, 3, 10**6, 64, 0, depth, 0.0, True, -1))
     test_quiet_chain_equals_oracle((wl.BCC, (6, 5, 4), 4, 2, 10**6, 100, 0, depth, 0.0, False, -1))
 
 
-@pytest.mark.parametrize("n,steps", [(1, 223), (1, 224), (2, 499), (2, 500), (16, 1479), (16, 1480), (17, 3000)])
+@pytest.mark.parametrize("n,steps", [(1, 223), (1, 224), (2, 749), (2, 750), (16, 1519), (16, 1520), (17, 3000)])
 @pytest.mark.parametrize("depth", [0, 99, 100, 380])
 def test_calls_around_the_least_steps(n, steps, depth):
     """The least steps and depth limit of a call that scans grow with its chains."""
@@ -112,7 +120,7 @@ def test_calls_around_the_least_steps(n, steps, depth):
 @pytest.mark.parametrize("B", [1, 3, 15, 16])
 @pytest.mark.parametrize("lattice,L,M,S,variant", [(wl.FCC, (4, 4, 4), 4, 2, -1), (wl.FCC, (3, 4, 5), 7, 3, 1),
                                                    (wl.BCC, (6, 5, 4), 3, 4, 2)])
-def test_few_candidates_a_step(lattice, L, M, S, variant, B):
+def test_few_candidates_a_step(lattice, L, M, S, variant, B, eager):
     """Below 16 candidates a step windows open after quiet steps only."""
     for mode, depth, tau in ((0, 0, 0.0), (1, 0, 0.0), (0, 13, 0.0), (0, 0, -1e-6)):
         test_quiet_chain_equals_oracle((lattice, L, M, S, 700 * B + B // 2, B, mode, depth, tau, False, variant))
